@@ -12,11 +12,13 @@ PKG = os.path.dirname(HERE)
 ROOT = os.path.dirname(PKG)
 OBJ_DIR = os.path.join(ROOT, "_build", "dels")
 LIB = os.path.join(PKG, "libdels.so")
-SOURCES = ["api.cpp", "combine.hip", "draft.hip", "accept.hip", "prepare.hip", "draft_persistent.hip", "prior.hip",
+SOURCES = ["api.cpp", "combine.hip", "draft.hip", "draft_small.hip", "accept.hip", "prepare.hip", "draft_persistent.hip", "prior.hip",
            "noalloc.hip", "uncertainty.hip", "peaks.hip",
            # the persistent kernel's instantiations, one unit per rank size and decoding mode
            "persist_greedy_r128.hip", "persist_greedy_r256.hip", "persist_sampled_r128.hip",
-           "persist_sampled_r256.hip"]
+           "persist_sampled_r256.hip",
+           # the launches per draft position, one unit per head type and decoding mode
+           "step_greedy_bf16.hip", "step_greedy_f32.hip", "step_sampled_bf16.hip", "step_sampled_f32.hip"]
 # the test build libdels_stress.so recompiles the units that include the persistent kernel with
 # DLS_STRESS_DELAYS (pauses before every hand-off publish) and reuses every other object
 STRESS_LIB = os.path.join(PKG, "libdels_stress.so")

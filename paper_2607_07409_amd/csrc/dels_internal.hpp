@@ -74,9 +74,8 @@ size_t uncertainty_workspace_bytes(int64_t rows, int32_t V);
 hipError_t launch_uncertainty(const UncArgs& a, hipStream_t st);
 
 struct DraftLayout {
-  int slice;       // vocabulary rows per workgroup of the LM-head phase
-  int groups;      // number of such workgroups
-  size_t off_h0, off_h1, off_rho, off_tok, off_part, total;
+  int groups;      // workgroups that share the vocabulary
+  size_t off_h0, off_h1, off_rho, off_part, total;
 };
 DraftLayout draft_layout(const dls_local_head& h, int32_t batch, int32_t B);
 
@@ -98,6 +97,8 @@ struct DraftArgs {
   const dls_row_uncertainty* unc;   // [batch, B] adaptive-fusion gates, or NULL (gate 1)
 };
 hipError_t launch_draft(const DraftArgs& a, hipStream_t st);
+bool small_head(const dls_local_head& h, int32_t B);   // drafted by one workgroup per sequence
+hipError_t launch_small(const DraftArgs& a, hipStream_t st);
 
 hipError_t launch_accept(const int32_t* draft, const int32_t* target, int32_t batch, int32_t B,
                          int32_t* out, hipStream_t st);

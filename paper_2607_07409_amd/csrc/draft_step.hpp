@@ -1,0 +1,1262 @@
+// One DeLS-Spec draft block per sequence (Algorithm 1, the decoding loop) as a chain of
+// launches per draft position j, for heads that are drafted with as they are:
+//
+//   k_gates   tokens u_j (argmax keys of position j-1), x = E[u_j], GRU cell -> h
+//   k_rank    rho = SiLU(W_rank h); further workgroups write the results of position j-1
+//   k_vocab   l_S = W_vocab rho, fused with the long logits, online LSEs, top-2; one argmax
+//             key and one partial per (sequence, workgroup)
+//
+// and k_finish for the last position.  A Markov head (rho = E_M[u_j]) needs k_vocab alone: every
+// workgroup gets the tokens and stages their rows itself.  The decoded token never leaves the
+// device and no launch waits for another one beyond the order of the stream.
+//
+// All products run on the matrix cores, 16 weight rows by 16 sequences at a time, with float32
+// accuracy (V = 151,936, d = 4,096, H = 1,024, r = 256, 32 sequences, 16 positions in bf16: 763 us a
+// block; one wave per weight row with vector instructions, four sequences at a time, took 10.5 ms,
+// and its error against float64 was larger): a float32 activation is split exactly into three bf16 values of 8 significant bits
+// (bf16 heads, v_mfma_f32_16x16x32_bf16), or multiplied as it is (float32 heads,
+// v_mfma_f32_16x16x4_f32).  Products of bf16 values are exact and the sums are float32.
+#pragma once
+#include <atomic>
+
+#include "dels_internal.hpp"
+
+namespace dls {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;   // arrays of it stay in registers
+
+constexpr int kST = 512;             // threads per workgroup
+constexpr int kSW = kST / 64;
+constexpr int kUnits = 5;            // hidden units per gates workgroup: 15 of 16 operand rows
+constexpr int kPairRows = 32;        // vocabulary rows a wave multiplies at a time (two operand tiles)
+
+// Statistics of one (sequence, workgroup) beside its argmax key.
+struct StepPart {
+  float lm, ls, sm, ss, fm, fs, t2;
+};
+
+// argmax key: orderable fused value over the complement of its index (equal values: lowest index)
+__device__ __forceinline__ uint64_t step_key(float t1, int i1) {
+  t1 += 0.0f;   // -0 -> +0, so that equal values compare equal
+  const uint32_t u = __float_as_uint(t1);
+  const uint32_t o = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((uint64_t)o << 32) | (uint32_t)~(uint32_t)i1;
+}
+__device__ __forceinline__ int step_key_index(uint64_t k) { return (int)~(uint32_t)k; }
+__device__ __forceinline__ float step_key_value(uint64_t k) {
+  const uint32_t o = (uint32_t)(k >> 32);
+  return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
+}
+__device__ __forceinline__ uint64_t u64_max(uint64_t a, uint64_t b) { return a > b ? a : b; }
+template <int N>
+__device__ __forceinline__ uint64_t u64_ror(uint64_t v) {   // within each row of 16 lanes
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, 0x120 + N, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), 0x120 + N, 0xf, 0xf, false);
+  return ((uint64_t)hi << 32) | lo;
+}
+__device__ __forceinline__ uint64_t wave_u64_max(uint64_t k) {
+  k = u64_max(k, u64_ror<8>(k));
+  k = u64_max(k, u64_ror<4>(k));
+  k = u64_max(k, u64_ror<2>(k));
+  k = u64_max(k, u64_ror<1>(k));
+  {
+    const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)k, (uint32_t)k, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(k >> 32), (uint32_t)(k >> 32), false, false);
+    k = u64_max(((uint64_t)hi[0] << 32) | lo[0], ((uint64_t)hi[1] << 32) | lo[1]);
+  }
+  {
+    const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)k, (uint32_t)k, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)(k >> 32), (uint32_t)(k >> 32), false, false);
+    k = u64_max(((uint64_t)hi[0] << 32) | lo[0], ((uint64_t)hi[1] << 32) | lo[1]);
+  }
+  return k;
+}
+
+// ----------------------------------------------------------------------------------
+// Matrix-core operands.  One 16-byte piece per lane is one operand chunk of KCH columns:
+// lane l holds row (or sequence) l % 16, columns KCH c + NP (l / 16) .. + NP - 1.  For float32
+// the four values of a piece feed four 16x16x4 products, whose column order both operands share.
+// ----------------------------------------------------------------------------------
+template <typename T> struct Op;
+template <> struct Op<bf16_t> {
+  static constexpr int KCH = 32, NP = 8, SPL = 3;
+  __device__ __forceinline__ static f32x4_t mma(uint4 a, uint4 b, f32x4_t c) {
+    union { uint4 u; bf16x8_t v; } x, y;
+    x.u = a;
+    y.u = b;
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x.v, y.v, c, 0, 0, 0);
+  }
+  // x = s[0] + s[1] + s[2] exactly: 8 significant bits each (truncated, so that no remainder
+  // changes sign or grows).  An infinity keeps its value in s[0] alone.
+  __device__ __forceinline__ static void split(const float* x, uint4* s) {
+    uint32_t p[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      uint32_t u[2][3];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float v = x[2 * i + e];
+        const uint32_t h = __float_as_uint(v) & 0xffff0000u;
+        const float r1 = fabsf(v) < INFINITY ? v - __uint_as_float(h) : 0.f;
+        const uint32_t m = __float_as_uint(r1) & 0xffff0000u;
+        u[e][0] = h;
+        u[e][1] = m;
+        u[e][2] = __float_as_uint(r1 - __uint_as_float(m));
+      }
+#pragma unroll
+      for (int q = 0; q < 3; ++q) p[q][i] = (u[0][q] >> 16) | (u[1][q] & 0xffff0000u);
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) s[q] = make_uint4(p[q][0], p[q][1], p[q][2], p[q][3]);
+  }
+};
+template <> struct Op<float> {
+  static constexpr int KCH = 16, NP = 4, SPL = 1;
+  __device__ __forceinline__ static f32x4_t mma(uint4 a, uint4 b, f32x4_t c) {
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+    return c;
+  }
+  __device__ __forceinline__ static void split(const float* x, uint4* s) {
+    s[0] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+  }
+};
+__device__ __forceinline__ uint4 sel4(bool p, uint4 v) {
+  return make_uint4(p ? v.x : 0u, p ? v.y : 0u, p ? v.z : 0u, p ? v.w : 0u);
+}
+// one piece of a float32 activation row (zeros unless ok), split for products with weights of type WT
+template <typename WT>
+__device__ __forceinline__ void act_split(const float4* v, bool ok, uint4* s) {
+  float x[Op<WT>::NP];
+#pragma unroll
+  for (int i = 0; i < Op<WT>::NP / 4; ++i) {
+    x[4 * i] = ok ? v[i].x : 0.f;
+    x[4 * i + 1] = ok ? v[i].y : 0.f;
+    x[4 * i + 2] = ok ? v[i].z : 0.f;
+    x[4 * i + 3] = ok ? v[i].w : 0.f;
+  }
+  Op<WT>::split(x, s);
+}
+// NB chunks c .. (below c1) of a weight row and of MT float32 activation rows: loaded in one go,
+// then acc[m] += their products.  Pieces past the range are zeros in both operands.
+template <typename WT, int MT, int NB>
+struct ActBatch {
+  using O = Op<WT>;
+  static constexpr int NF = O::NP / 4;
+  u32x4_t w[NB];
+  f32x4_t x[MT][NB][NF];
+  __device__ __forceinline__ void load(const WT* wr, const float* const* xr, int K, int c, int c1, int g) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int kk = (c + i) * O::KCH + g * O::NP;
+      const int k = c + i < c1 && kk < K ? kk : 0;
+      w[i] = *reinterpret_cast<const u32x4_t*>(wr + k);
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) x[m][i][f] = *reinterpret_cast<const f32x4_t*>(xr[m] + k + 4 * f);
+    }
+  }
+  __device__ __forceinline__ void use(int K, int c, int c1, int g, f32x4_t* acc) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const bool ok = c + i < c1 && (c + i) * O::KCH + g * O::NP < K;
+      const uint4 wi = sel4(ok, make_uint4(w[i].x, w[i].y, w[i].z, w[i].w));
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        float4 v[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f] = make_float4(x[m][i][f].x, x[m][i][f].y, x[m][i][f].z, x[m][i][f].w);
+        uint4 s[O::SPL];
+        act_split<WT>(v, ok, s);
+#pragma unroll
+        for (int e = O::SPL - 1; e >= 0; --e) acc[m] = O::mma(wi, s[e], acc[m]);
+      }
+    }
+  }
+};
+
+// the tokens decoded at the position before: the largest of a sequence's G <= kMaxG keys, or the
+// caller's token of the first position
+struct TokenSource {
+  const uint64_t* keys;     // [batch][G], or NULL: last
+  const int32_t* last;
+  int G;
+};
+// Keys of the wave's sequences b0 + wave, b0 + wave + kSW, ..: every load is issued before the
+// first is waited for.
+template <int NS>
+struct TokenKeys {
+  uint64_t k[NS][kMaxG / 64];
+};
+template <int NS>
+__device__ __forceinline__ void load_keys(const TokenSource& ts, int b0, int batch, int wave, int lane, TokenKeys<NS>& tk) {
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int b = min(b0 + wave + s * kSW, batch - 1);
+    if (ts.keys) {
+#pragma unroll
+      for (int i = 0; i < kMaxG / 64; ++i) tk.k[s][i] = ts.keys[(size_t)b * ts.G + min(lane + 64 * i, ts.G - 1)];
+    } else {
+      tk.k[s][0] = (uint32_t)~(uint32_t)ts.last[b];
+#pragma unroll
+      for (int i = 1; i < kMaxG / 64; ++i) tk.k[s][i] = 0;
+    }
+  }
+}
+template <int NS>
+__device__ __forceinline__ void merge_keys(const TokenKeys<NS>& tk, int V, int wave, int lane, int* s_tok) {
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    uint64_t k = tk.k[s][0];
+#pragma unroll
+    for (int i = 1; i < kMaxG / 64; ++i) k = u64_max(k, tk.k[s][i]);
+    const int t = step_key_index(wave_u64_max(k));
+    if (lane == 0) s_tok[wave + s * kSW] = (unsigned)t < (unsigned)V ? t : 0;   // out of range, or every value -inf
+  }
+}
+
+// ----------------------------------------------------------------------------------
+// The results of one position: the G keys and parts of a sequence, merged by one workgroup.
+// ----------------------------------------------------------------------------------
+struct FinishArgs {
+  const uint64_t* keys;
+  const StepPart* parts;
+  int G, j, B, batch;
+  float wl, al;
+  int long_only;
+  int32_t* out_tokens;
+  dls_row_stats* out_stats;
+  Sampler smp;
+  const dls_row_uncertainty* unc;
+};
+__device__ __forceinline__ void finish_row(const FinishArgs& f, int b, Partial* sh) {
+  Partial P = partial_empty();
+  for (int i = threadIdx.x; i < f.G; i += kST) {
+    const uint64_t k = f.keys[(size_t)b * f.G + i];
+    const StepPart s = f.parts[(size_t)b * f.G + i];
+    Partial Q;
+    Q.L = {s.lm, s.ls};
+    Q.S = {s.sm, s.ss};
+    Q.F = {s.fm, s.fs};
+    Q.t1 = step_key_value(k);
+    Q.i1 = step_key_index(k);
+    Q.t2 = s.t2;
+    Q.pad = 0;
+    P = partial_merge(P, Q);
+  }
+  P = block_merge(P, sh, kSW);
+  if (threadIdx.x == 0) {
+    int32_t t;
+    const int ti = P.i1 == 0x7fffffff ? 0 : P.i1;
+    const float alb = f.unc ? f.al * f.unc[(size_t)b * f.B + f.j].gate : f.al;
+    finalize_row(P, f.wl, alb, f.long_only != 0, &t, f.out_stats ? f.out_stats + (size_t)b * f.B + f.j : nullptr,
+                 nullptr, f.smp.inv_temp != 0.f ? gumbel_at(f.smp, b, f.j, ti) : 0.f, f.smp.temp);
+    f.out_tokens[(size_t)b * f.B + f.j] = t;
+  }
+}
+__global__ __launch_bounds__(kST) void k_finish(FinishArgs f) {
+  __shared__ Partial sh[kSW];
+  finish_row(f, blockIdx.x, sh);
+}
+
+// ----------------------------------------------------------------------------------
+// GRU cell.  A workgroup owns kUnits hidden units (15 gate rows of W_ih and W_hh: one operand
+// tile) and 16 MT sequences; its eight waves take an eighth of the columns each and
+// add their partial products in a fixed order.
+// ----------------------------------------------------------------------------------
+template <typename WT>
+struct GatesArgs {
+  const WT *emb, *w_ih, *w_hh;
+  int d, H, V, batch;
+  TokenSource ts;
+  const float* h_in;
+  int h_zero;
+  float* h_out;
+};
+template <typename WT, int MT>
+__global__ __launch_bounds__(kST, 2) void k_gates(GatesArgs<WT> a) {
+  using O = Op<WT>;
+  constexpr int NW = 16, NX = MT > 1 ? 4 : 8;   // chunks of W_ih and of x in flight
+  constexpr int NH = MT > 2 ? 2 : 4;            // chunks of W_hh and h
+  __shared__ int s_tok[16 * MT];
+  __shared__ f32x4_t red[kSW][MT][64];    // rows of r and z: input + recurrent; of n: input
+  __shared__ f32x4_t redn[kSW][MT][32];   // rows 8 to 15: recurrent (rows of n: 10 to 14)
+  static_assert(kUnits * 3 <= 16 && kUnits * 2 >= 8, "operand rows of the n gate lie in the upper half");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, g = lane >> 4;
+  const int b0 = blockIdx.y * 16 * MT;
+  const int d = a.d, H = a.H;
+  const int u0 = blockIdx.x * kUnits;
+  const int q = min(n / kUnits, 2), unit = min(u0 + n % kUnits, H - 1);   // row n of the operand tile
+  f32x4_t ax[MT], ah[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) ax[m] = ah[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+  TokenKeys<2 * MT> tk;
+  load_keys(a.ts, b0, a.batch, wave, lane, tk);
+  asm volatile("" ::: "memory");
+  // everything that does not depend on the tokens is asked for while their keys are on the way
+  const int nch = (H + O::KCH - 1) / O::KCH;
+  const int ch0 = nch * wave / kSW, ch1 = nch * (wave + 1) / kSW;
+  const WT* wh = a.w_hh + (size_t)(q * H + unit) * H;
+  const float* hr[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) hr[m] = a.h_in + (size_t)min(b0 + 16 * m + n, a.batch - 1) * H;
+  ActBatch<WT, MT, NH> hb;
+  if (!a.h_zero) hb.load(wh, hr, H, ch0, ch1, g);
+  const int ncx = (d + O::KCH - 1) / O::KCH;
+  const int cx0 = ncx * wave / kSW, cx1 = ncx * (wave + 1) / kSW;
+  const WT* wx = a.w_ih + (size_t)(q * H + unit) * d;
+  auto col = [&](int c) {   // first column of the lane's piece of chunk c (0 past the wave's range)
+    const int k = c * O::KCH + g * O::NP;
+    return c < cx1 && k < d ? k : 0;
+  };
+  uint4 w[NW];
+  auto load_wx = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < NW; ++i) w[i] = *reinterpret_cast<const uint4*>(wx + col(c + i));
+  };
+  load_wx(cx0);
+  asm volatile("" ::: "memory");
+  merge_keys(tk, a.V, wave, lane, s_tok);
+  __syncthreads();
+  const WT* xr[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) xr[m] = a.emb + (size_t)s_tok[16 * m + n] * d;
+  uint4 x[MT][NX];
+  auto load_x = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < NX; ++i)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) x[m][i] = *reinterpret_cast<const uint4*>(xr[m] + col(c + i));
+  };
+  load_x(cx0);
+  asm volatile("" ::: "memory");
+  if (!a.h_zero) {
+    hb.use(H, ch0, ch1, g, ah);
+    for (int c = ch0 + NH; c < ch1; c += NH) {
+      hb.load(wh, hr, H, c, ch1, g);
+      hb.use(H, c, ch1, g, ah);
+    }
+  }
+  for (int c = cx0; c < cx1; c += NW) {
+    if (c > cx0) load_wx(c);
+#pragma unroll
+    for (int h = 0; h < NW / NX; ++h) {
+      if (c + h * NX < cx1) {
+        if (c > cx0 || h) load_x(c + h * NX);
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+          const int ci = c + h * NX + i;
+          const bool ok = ci < cx1 && ci * O::KCH + g * O::NP < d;
+          const uint4 wi = sel4(ok, w[h * NX + i]);
+#pragma unroll
+          for (int m = 0; m < MT; ++m) ax[m] = O::mma(wi, sel4(ok, x[m][i]), ax[m]);
+        }
+      }
+    }
+  }
+  // D layout: lane 16 (row / 4) + column holds row % 4 of its four values
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) red[wave][m][lane][e] = 4 * g + e < 2 * kUnits ? ax[m][e] + ah[m][e] : ax[m][e];
+    if (lane >= 32) redn[wave][m][lane - 32] = ah[m];
+  }
+  __syncthreads();
+  for (int i = tid; i < 16 * MT * kUnits; i += kST) {
+    const int s = i % (16 * MT), u = i / (16 * MT);
+    const int b = b0 + s;
+    if (b >= a.batch || u0 + u >= H) continue;
+    const float hp = a.h_zero ? 0.f : a.h_in[(size_t)b * H + u0 + u];
+    float sx[3], sn = 0.f;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      const int row = e * kUnits + u;
+      const int l = 16 * (row >> 2) + (s & 15);
+      sx[e] = 0.f;
+#pragma unroll
+      for (int v = 0; v < kSW; ++v) {
+        sx[e] += red[v][s >> 4][l][row & 3];
+        if (e == 2) sn += redn[v][s >> 4][l - 32][row & 3];
+      }
+    }
+    const float rg = sigmoidf_(sx[0]), zg = sigmoidf_(sx[1]);
+    const float ng = tanhf_(sx[2] + rg * sn);
+    a.h_out[(size_t)b * H + u0 + u] = (1.f - zg) * ng + zg * hp;
+  }
+}
+
+// ----------------------------------------------------------------------------------
+// rho = SiLU(W_rank h), 16 rank rows by 16 sequences per workgroup (columns split over the
+// waves); the workgroups after them write the results of the position before (fin.batch of
+// them, none at the first position).
+// ----------------------------------------------------------------------------------
+template <typename WT>
+struct RankArgs {
+  const WT* w_rank;
+  int H, r, batch, tiles;   // tiles = ceil(r / 16) * ceil(batch / 16)
+  const float* h;
+  float* rho;
+};
+template <typename WT>
+__global__ __launch_bounds__(kST) void k_rank(RankArgs<WT> a, FinishArgs fin) {
+  using O = Op<WT>;
+  __shared__ f32x4_t red[kSW][64];
+  __shared__ Partial sh[kSW];
+  if ((int)blockIdx.x >= a.tiles) {
+    finish_row(fin, blockIdx.x - a.tiles, sh);
+    return;
+  }
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, g = lane >> 4;
+  const int rt = (a.r + 15) >> 4;
+  const int r0 = (blockIdx.x % rt) * 16, b0 = (blockIdx.x / rt) * 16;
+  const WT* wr = a.w_rank + (size_t)min(r0 + n, a.r - 1) * a.H;
+  const float* hr = a.h + (size_t)min(b0 + n, a.batch - 1) * a.H;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  const int nc = (a.H + O::KCH - 1) / O::KCH;
+  const int c0 = nc * wave / kSW, c1 = nc * (wave + 1) / kSW;
+  for (int c = c0; c < c1; c += 4) {
+    ActBatch<WT, 1, 4> hb;
+    hb.load(wr, &hr, a.H, c, c1, g);
+    hb.use(a.H, c, c1, g, &acc);
+  }
+  red[wave][lane] = acc;
+  __syncthreads();
+  if (tid < 256) {
+    const int row = tid & 15, s = tid >> 4;
+    const int l = 16 * (row >> 2) + s;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSW; ++w) v += red[w][l][row & 3];
+    if (b0 + s < a.batch && r0 + row < a.r) a.rho[(size_t)(b0 + s) * a.r + r0 + row] = siluf_(v);
+  }
+}
+
+// ----------------------------------------------------------------------------------
+// Vocabulary head and fusion.
+// ----------------------------------------------------------------------------------
+template <typename WT, typename LT>
+struct VocabArgs {
+  const WT* w_vocab;
+  int V, r, batch, G, np;        // np = ceil(V / kPairRows)
+  const float* rho;              // RNN head
+  const WT* e_m;                 // Markov head (then ts holds the tokens)
+  TokenSource ts;
+  const LT* L;                   // row of sequence 0 at this position
+  size_t bstride;
+  const float* prior;
+  float wl, al, be;
+  int long_only;
+  int j, B;
+  Sampler smp;
+  const dls_row_uncertainty* unc;
+  uint64_t* keys;
+  StepPart* parts;
+  int finish;                    // the workgroups also write the results of the position before
+};
+
+struct __attribute__((packed, aligned(2))) Raw16 { uint32_t x, y, z, w; };
+// eight consecutive long logits (any alignment of the element type)
+__device__ __forceinline__ void load8(const bf16_t* p, uint4* o) {
+  const Raw16 v = *reinterpret_cast<const Raw16*>(p);
+  o[0] = make_uint4(v.x, v.y, v.z, v.w);
+}
+struct __attribute__((packed, aligned(4))) Raw32 { uint32_t v[8]; };
+__device__ __forceinline__ void load8(const float* p, uint4* o) {
+  const Raw32 v = *reinterpret_cast<const Raw32*>(p);
+  o[0] = make_uint4(v.v[0], v.v[1], v.v[2], v.v[3]);
+  o[1] = make_uint4(v.v[4], v.v[5], v.v[6], v.v[7]);
+}
+__device__ __forceinline__ void widen8(const uint4* o, float* x, bf16_t) { Chunk<bf16_t>::widen(o[0], x); }
+__device__ __forceinline__ void widen8(const uint4* o, float* x, float) {
+  Chunk<float>::widen(o[0], x);
+  Chunk<float>::widen(o[1], x + 4);
+}
+
+// one lane's running statistics of one sequence (finite-start log-sum-exps)
+__device__ __forceinline__ void push8(Lse& a, const float* x) {
+  const float m = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(x[4], x[5]), fmaxf(x[6], x[7])));
+  lse_fold_fin<8>(a, x, m);
+}
+
+// a finite-start state without an entry becomes the empty one (a NaN sum is kept)
+__device__ __forceinline__ void close_lse(Lse& a) { a.m = a.s == 0.f ? -INFINITY : a.m; }
+
+template <int N>
+struct PermN {   // N consecutive lanes
+  template <typename F>
+  __device__ __forceinline__ void each(F f) const {
+#pragma unroll
+    for (int m = N / 2; m >= 1; m >>= 1) f(m);
+  }
+  __device__ __forceinline__ float operator()(float v, int m) const { return __shfl_xor(v, m); }
+  __device__ __forceinline__ int i(int v, int m) const { return __shfl_xor(v, m); }
+};
+struct Perm4Rows {   // lanes l, l ^ 16, l ^ 32, l ^ 48
+  template <typename F>
+  __device__ __forceinline__ void each(F f) const {
+    f(32);
+    f(16);
+  }
+  __device__ __forceinline__ float operator()(float v, int m) const { return __shfl_xor(v, m); }
+  __device__ __forceinline__ int i(int v, int m) const { return __shfl_xor(v, m); }
+};
+
+// r above 256: the activations of 16 MT sequences stay in LDS as operands, and KCB chunks of a pair
+// of tiles are loaded at a time (nkb rounds cover r).
+template <typename WT, typename LT, int MT, int KCB, int SPL, bool SAMPLE>
+__global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, FinishArgs fin, int nkb) {
+  using O = Op<WT>;
+  constexpr int NL = sizeof(LT) == 2 ? 1 : 2;   // 16-byte pieces of eight long logits
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ int s_tok[16 * MT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, g = lane >> 4;
+  const int b0 = blockIdx.y * 16 * MT;
+  const int V = a.V, r = a.r;
+  const int gw = blockIdx.x * kSW + wave, tw = a.G * kSW;
+  const int p0 = (int)((int64_t)a.np * gw / tw), p1 = (int)((int64_t)a.np * (gw + 1) / tw);
+
+  // Rows of a pair: lane row n of tile i is vocabulary row 32 p + 8 (n / 4) + 4 i + n % 4, so that
+  // a lane's results (rows 4g + e of both tiles) are the eight consecutive entries 32 p + 8 g + ..
+  struct Pair {
+    uint4 A[2][KCB];
+    uint4 L[MT][NL];
+  };
+  auto load_w = [&](Pair& t, int p, int kb) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int row = min(kPairRows * p + 8 * (n >> 2) + 4 * i + (n & 3), V - 1);
+      const WT* wr = a.w_vocab + (size_t)row * r;
+#pragma unroll
+      for (int c = 0; c < KCB; ++c) {
+        const int k = (kb * KCB + c) * O::KCH + g * O::NP;
+        t.A[i][c] = *reinterpret_cast<const uint4*>(wr + (k < r ? k : 0));
+      }
+    }
+  };
+  auto load_pair = [&](Pair& t, int p) {
+    if (p >= p1) return;
+    if (kPairRows * (p + 1) <= V) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m)
+        load8(a.L + (size_t)min(b0 + 16 * m + n, a.batch - 1) * a.bstride + kPairRows * p + 8 * g, t.L[m]);
+    }
+    if (!a.long_only) load_w(t, p, 0);
+  };
+  // two pairs in flight where the registers allow
+  constexpr bool DEEP = false;
+  const bool rfull = r == nkb * KCB * O::KCH;
+  Pair t0, t1;
+
+  // activations of the 16 MT sequences as operands in LDS: [m][chunk][split][lane] of 16 bytes.
+  // Loads return in order: the activations are asked for before the weights, which then arrive
+  // while the operands are staged.
+  uint4* s_b = reinterpret_cast<uint4*>(smem);
+  const int kc = nkb * KCB;
+  auto put = [&](int i, const uint4* o) {
+    const int s = i / (kc * 4), pc = i % (kc * 4);
+#pragma unroll
+    for (int e = 0; e < SPL; ++e)
+      s_b[(((size_t)(s >> 4) * kc + (pc >> 2)) * SPL + e) * 64 + 16 * (pc & 3) + (s & 15)] = o[e];
+  };
+  auto piece_ok = [&](int i) { return (i % (kc * 4)) * O::NP < r && b0 + i / (kc * 4) < a.batch; };
+  auto piece_col = [&](int i) { return (i % (kc * 4)) * O::NP < r ? (i % (kc * 4)) * O::NP : 0; };
+  constexpr int NQ = (16 * MT * KCB * 4 + kST - 1) / kST, NF = O::NP / 4;   // pieces per thread of one round
+  const int pieces = a.long_only ? 0 : 16 * MT * kc * 4;
+  if (!a.long_only && a.e_m) {
+    TokenKeys<2 * MT> tk;
+    load_keys(a.ts, b0, a.batch, wave, lane, tk);
+    asm volatile("" ::: "memory");
+    load_pair(t0, p0);
+    asm volatile("" ::: "memory");
+    merge_keys(tk, V, wave, lane, s_tok);
+    __syncthreads();
+    for (int i = tid; i < pieces; i += kST) {
+      const uint4 o = sel4(piece_ok(i), *reinterpret_cast<const uint4*>(a.e_m + (size_t)s_tok[i / (kc * 4)] * r + piece_col(i)));
+      put(i, &o);
+    }
+    if (DEEP) load_pair(t1, p0 + 1);
+  } else {
+    float4 v[NQ][NF];
+    const float* rho0 = a.rho;
+    if (!a.long_only) {
+#pragma unroll
+      for (int qi = 0; qi < NQ; ++qi) {
+        const int i = min(tid + qi * kST, pieces - 1);
+        const float* row = rho0 + (size_t)min(b0 + i / (kc * 4), a.batch - 1) * r + piece_col(i);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[qi][f] = *reinterpret_cast<const float4*>(row + 4 * f);
+      }
+      asm volatile("" ::: "memory");
+    }
+    load_pair(t0, p0);
+    if (DEEP) load_pair(t1, p0 + 1);
+    if (!a.long_only) {
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int qi = 0; qi < NQ; ++qi) {
+        const int i = tid + qi * kST;
+        uint4 o[O::SPL];
+        act_split<WT>(v[qi], i < pieces && piece_ok(i), o);
+        if (i < pieces) put(i, o);
+      }
+      for (int i = tid + NQ * kST; i < pieces; i += kST) {   // r > 256 (bf16) or 128 (float32)
+        const float* row = rho0 + (size_t)min(b0 + i / (kc * 4), a.batch - 1) * r + piece_col(i);
+        float4 t[NF];
+#pragma unroll
+        for (int f = 0; f < NF; ++f) t[f] = *reinterpret_cast<const float4*>(row + 4 * f);
+        uint4 o[O::SPL];
+        act_split<WT>(t, piece_ok(i), o);
+        put(i, o);
+      }
+    }
+  }
+  __syncthreads();
+
+  Partial P[MT];
+  float alb[MT], beb[MT];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    P[m] = partial_empty();
+    P[m].L.m = P[m].S.m = P[m].F.m = kFinMin;
+    const int b = min(b0 + 16 * m + n, a.batch - 1);
+    const float gt = a.unc ? a.unc[(size_t)b * a.B + a.j].gate : 1.f;
+    alb[m] = a.al * gt;
+    beb[m] = a.be * gt;
+  }
+
+  auto process = [&](Pair& t, int p, int ahead) {
+    const int v0 = kPairRows * p + 8 * g;
+    const bool whole = kPairRows * (p + 1) <= V;   // uniform
+    float pr[8];
+    if (whole && a.prior) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pr[e] = a.prior[v0 + e];
+    }
+    uint4 lraw[MT][NL];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int i = 0; i < NL; ++i) lraw[m][i] = t.L[m][i];
+    f32x4_t acc[MT][2];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[m][0] = acc[m][1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (!a.long_only) {
+      for (int kb = 0; kb < nkb; ++kb) {
+        if (kb) load_w(t, p, kb);
+        if (!rfull) {   // columns past r: zero in both operands
+#pragma unroll
+          for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < KCB; ++c) t.A[i][c] = sel4((kb * KCB + c) * O::KCH + g * O::NP < r, t.A[i][c]);
+        }
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+          const uint4* sb = s_b + ((size_t)m * kc + kb * KCB) * SPL * 64 + lane;
+#pragma unroll
+          for (int c = 0; c < KCB; ++c)
+#pragma unroll
+            for (int e = SPL - 1; e >= 0; --e) {
+              const uint4 bb = sb[(c * SPL + e) * 64];
+              acc[m][0] = O::mma(t.A[0][c], bb, acc[m][0]);
+              acc[m][1] = O::mma(t.A[1][c], bb, acc[m][1]);
+            }
+        }
+      }
+    }
+    load_pair(t, p + ahead);   // in flight during the fold
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+      float x[8], s[8], f[8];
+      const int b = b0 + 16 * m + n;
+      if (whole) {
+        widen8(lraw[m], x, LT());
+      } else {
+        const LT* lr = a.L + (size_t)min(b, a.batch - 1) * a.bstride;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = to_f32(lr[min(v0 + e, V - 1)]);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        s[e] = acc[m][e >> 2][e & 3];
+        f[e] = a.wl == 0.f ? 0.f : a.wl * x[e];
+      }
+      if (!a.long_only) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] = __builtin_fmaf(alb[m], s[e], f[e]);
+        if (a.prior) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) f[e] = minus_weighted(f[e], beb[m], whole ? pr[e] : a.prior[min(v0 + e, V - 1)]);
+        }
+      }
+      if (SAMPLE) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) f[e] *= a.smp.inv_temp;
+      }
+      if (!whole) {   // entries past the vocabulary (lanes past the batch repeat its last sequence)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const bool in = v0 + e < V;
+          x[e] = in ? x[e] : -INFINITY;
+          s[e] = in ? s[e] : -INFINITY;
+          f[e] = in ? f[e] : -INFINITY;
+        }
+      }
+      push8(P[m].L, x);
+      if (!a.long_only) push8(P[m].S, s);
+      push8(P[m].F, f);
+      if (SAMPLE) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const uint4 w4 = philox_row(a.smp, b, a.j, v0 + 4 * h);
+          f[4 * h] += gumbel_from_word(w4.x);
+          f[4 * h + 1] += gumbel_from_word(w4.y);
+          f[4 * h + 2] += gumbel_from_word(w4.z);
+          f[4 * h + 3] += gumbel_from_word(w4.w);
+        }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) top2_push(P[m], f[e], v0 + e);
+    }
+  };
+  if (DEEP) {
+    for (int p = p0; p < p1; p += 2) {
+      process(t0, p, 2);
+      if (p + 1 < p1) process(t1, p + 1, 2);
+    }
+  } else {
+    for (int p = p0; p < p1; ++p) process(t0, p, 1);
+  }
+
+  // merge: the four row groups of a wave, then the eight waves through LDS
+  __syncthreads();
+  Partial* sp = reinterpret_cast<Partial*>(smem);   // [wave][16 MT]
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    close_lse(P[m].L);
+    close_lse(P[m].S);
+    close_lse(P[m].F);
+    const Partial Q = allred_partial(P[m], Perm4Rows{});
+    if (g == 0) sp[wave * 16 * MT + 16 * m + n] = Q;
+  }
+  __syncthreads();
+  for (int i = tid; i < 16 * MT * kSW; i += kST) {   // whole waves
+    const int s = i >> 3, w = i & 7;
+    const Partial Q = allred_partial(sp[w * 16 * MT + s], PermN<8>{});
+    if (w == 0 && b0 + s < a.batch) {
+      const size_t o = (size_t)(b0 + s) * a.G + blockIdx.x;
+      a.keys[o] = step_key(Q.t1, Q.i1);
+      a.parts[o] = StepPart{Q.L.m, Q.L.s, Q.S.m, Q.S.s, Q.F.m, Q.F.s, Q.t2};
+    }
+  }
+  if (a.finish && blockIdx.y == 0) {   // uniform
+    __syncthreads();
+    for (int row = blockIdx.x; row < a.batch; row += a.G) finish_row(fin, row, sp);
+  }
+}
+
+// ----------------------------------------------------------------------------------
+// Vocabulary head for r <= 256.  Every wave keeps the activations of one tile of 16 sequences in
+// registers as operands (KC chunks of SPL values) and folds one vocabulary tile of 16 rows at a
+// time.  MT tiles of sequences share a workgroup: wave w serves sequence tile w % MT and, of the
+// NSTR = 8 / MT vocabulary tiles of a step, tile w / MT.
+//
+// The stream of weights bounds the loop, so each weight is loaded once per workgroup, PD steps
+// ahead and in memory order (whole kilobytes per instruction: 6.3 TB/s of a 78 MB matrix that is
+// read over and over, against 5.2 TB/s for operand-shaped loads of 16 rows by 64 bytes), and turned
+// into operands through LDS.  Every other position runs through the steps backwards, so that the
+// end of the matrix is still in L2 (7.9 TB/s).
+//
+// LDS slot of a piece (row m of the tile, piece pc of the row): 16 pc + (m ^ pc % 16), so that
+// neither the row-wise stores nor the operand-wise reads meet in a bank.
+// ----------------------------------------------------------------------------------
+template <typename LT> struct Four;
+template <> struct Four<bf16_t> {   // four consecutive long logits at any alignment of their type
+  struct __attribute__((packed, aligned(2))) raw { uint32_t x, y; };
+  typedef uint2 type;
+  __device__ __forceinline__ static type load(const bf16_t* p) {
+    const raw v = *reinterpret_cast<const raw*>(p);
+    return make_uint2(v.x, v.y);
+  }
+  __device__ __forceinline__ static void widen(type v, float* x) {
+    x[0] = bf16_lo(v.x);
+    x[1] = bf16_hi(v.x);
+    x[2] = bf16_lo(v.y);
+    x[3] = bf16_hi(v.y);
+  }
+};
+template <> struct Four<float> {
+  struct __attribute__((packed, aligned(4))) raw { float x, y, z, w; };
+  typedef float4 type;
+  __device__ __forceinline__ static type load(const float* p) {
+    const raw v = *reinterpret_cast<const raw*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+  }
+  __device__ __forceinline__ static void widen(type v, float* x) {
+    x[0] = v.x;
+    x[1] = v.y;
+    x[2] = v.z;
+    x[3] = v.w;
+  }
+};
+__device__ __forceinline__ void push4(Lse& a, const float* x) {
+  lse_fold_fin<4>(a, x, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+}
+
+constexpr int kPriorTiles = 128;   // tiles of prior entries a workgroup keeps in LDS (8 KB)
+template <int MT, int KC, bool SAMPLE>
+struct VocabPlan {
+  static constexpr int NSTR = kSW / MT;
+  static constexpr int NP = NSTR * KC / kSW;                      // 16-byte pieces per thread and step
+  // as deep as the registers allow without spills (the noise of a sampled row takes some)
+  static constexpr int PD = NP >= 16 ? 1 : NP >= 8 ? (SAMPLE ? 1 : 2) : NP >= 4 ? 3 : NP >= 2 ? 6 : 8;
+  static constexpr int kTile = KC * 64;                           // pieces of a tile in LDS
+  static constexpr int kBufs = MT == 1 ? 1 : 2;                   // a wave alone needs no second buffer
+  static constexpr size_t kLds = (size_t)kBufs * NSTR * kTile * 16;
+  static constexpr size_t act(int spl) { return (size_t)MT * KC * spl * 1024; }
+};
+
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE>
+__global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArgs fin) {
+  using O = Op<WT>;
+  using PL = VocabPlan<MT, KC, SAMPLE>;
+  constexpr int NSTR = PL::NSTR, NP = PL::NP, PD = PL::PD, NF = O::NP / 4, kTile = PL::kTile;
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  __shared__ int s_tok[16 * MT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, g = lane >> 4;
+  const int b0 = blockIdx.y * 16 * MT;
+  const int V = a.V, r = a.r, pr = r / O::NP;   // pieces of a row
+  const uint32_t nt = (uint32_t)(V + 15) >> 4;
+  const int T0 = (int)(nt * blockIdx.x / (uint32_t)a.G), T1 = (int)(nt * (blockIdx.x + 1) / (uint32_t)a.G);
+  const int steps = (T1 - T0 + NSTR - 1) / NSTR;
+  const int mt = wave % MT, str = wave / MT;
+  const int b = b0 + 16 * mt + n, bc = min(b, a.batch - 1);
+  const LT* lrow = a.L + (size_t)bc * a.bstride;
+  u32x4_t* s_w = reinterpret_cast<u32x4_t*>(smem);
+  const bool rev = (a.j & 1) != 0;
+
+  // Pieces of a step are dealt out in memory order: with MT = 1 a wave takes its own tile, else the
+  // workgroup the whole step.  Row and column of piece p from a reciprocal: exact for p < 4096 and
+  // pr <= 64 (p times its error stays below 2^18).
+  const uint32_t recip = ((1u << 18) + (uint32_t)pr - 1) / (uint32_t)pr;
+  static_assert(kST * NP <= 4096 || MT == 1, "pieces of a step");
+  auto piece = [&](int q) { return MT == 1 ? q * 64 + lane : q * kST + tid; };
+  const int wbase = MT == 1 ? str * 16 * pr : 0;
+  const int last = (V - 1) * pr + pr - 1;
+  u32x4_t w[PD][NP];
+  typename Four<LT>::type lg[PD];
+  auto load_step = [&](int u, int i) {
+    if (i >= steps) return;   // uniform
+    const int ii = rev ? steps - 1 - i : i;
+    const int first = (T0 + ii * NSTR) * 16 * pr;
+#pragma unroll
+    for (int q = 0; q < NP; ++q)   // past the matrix: its last piece, for rows that are not folded
+      w[u][q] = *reinterpret_cast<const u32x4_t*>(a.w_vocab + (size_t)min(first + wbase + piece(q), last) * O::NP);
+    const int t = T0 + ii * NSTR + str;
+    if (16 * t + 16 <= V) lg[u] = Four<LT>::load(lrow + 16 * t + 4 * g);
+  };
+
+  // Activations as operands, [sequence tile][chunk][split][lane] in LDS and from there into
+  // registers.  Loads return in order: they are asked for before the weights, which then arrive
+  // while the operands are made.
+  // The workgroup's slice of the prior goes to LDS with them.
+  constexpr int NA = (MT * KC * 64 + kST - 1) / kST;
+  float* s_prior = reinterpret_cast<float*>(smem + PL::kLds);
+  const bool staged = a.prior && T1 - T0 + NSTR <= kPriorTiles;   // also read by waves past the last tile
+  float pv0[kPriorTiles * 16 / kST];
+  if (staged) {
+#pragma unroll
+    for (int q = 0; q < kPriorTiles * 16 / kST; ++q) pv0[q] = a.prior[min(16 * T0 + tid + q * kST, V - 1)];
+  }
+  uint4* s_a = reinterpret_cast<uint4*>(smem);
+  uint4 act[KC][SPL];
+  {
+    auto put = [&](int i, const uint4* o) {   // piece i: sequence i / (4 KC), piece i % (4 KC) of its row
+      const int s = i / (4 * KC), pc = i % (4 * KC);
+#pragma unroll
+      for (int e = 0; e < SPL; ++e) s_a[(((s >> 4) * KC + (pc >> 2)) * SPL + e) * 64 + 16 * (pc & 3) + (s & 15)] = o[e];
+    };
+    if (a.e_m) {
+      TokenKeys<2 * MT> tk;
+      load_keys(a.ts, b0, a.batch, wave, lane, tk);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int u = 0; u < PD / 2; ++u) load_step(u, u);
+      asm volatile("" ::: "memory");
+      merge_keys(tk, V, wave, lane, s_tok);
+      __syncthreads();
+      uint4 v[NA];
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+        const int i = min(tid + q * kST, MT * KC * 64 - 1), pc = i % (4 * KC);
+        v[q] = sel4(pc < pr, *reinterpret_cast<const uint4*>(a.e_m + ((size_t)s_tok[i / (4 * KC)] * pr + (pc < pr ? pc : 0)) * O::NP));
+      }
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int u = PD / 2; u < PD; ++u) load_step(u, u);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < NA; ++q)
+        if (tid + q * kST < MT * KC * 64) put(tid + q * kST, &v[q]);
+    } else {
+      float4 v[NA][NF];
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+        const int i = min(tid + q * kST, MT * KC * 64 - 1), pc = i % (4 * KC);
+        const float* row = a.rho + ((size_t)min(b0 + i / (4 * KC), a.batch - 1) * pr + (pc < pr ? pc : 0)) * O::NP;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[q][f] = *reinterpret_cast<const float4*>(row + 4 * f);
+      }
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int u = 0; u < PD; ++u) load_step(u, u);
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
+        const int i = tid + q * kST;
+        uint4 o[O::SPL];
+        act_split<WT>(v[q], i % (4 * KC) < pr, o);
+        if (i < MT * KC * 64) put(i, o);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int e = 0; e < SPL; ++e) act[c][e] = s_a[((mt * KC + c) * SPL + e) * 64 + lane];
+    __syncthreads();
+    if (staged) {
+#pragma unroll
+      for (int q = 0; q < kPriorTiles * 16 / kST; ++q) s_prior[tid + q * kST] = pv0[q];
+      __syncthreads();
+    }
+    if (pr < 4 * KC) {   // columns past r: zero in both operands
+      for (int i = tid; i < (int)(PL::kLds / 16); i += kST) s_w[i] = u32x4_t{0u, 0u, 0u, 0u};
+      __syncthreads();
+    }
+  }
+
+  Partial P = partial_empty();
+  P.L.m = P.S.m = P.F.m = kFinMin;
+  const float gate = a.unc ? a.unc[(size_t)bc * a.B + a.j].gate : 1.f;
+  const float alb = a.al * gate, beb = a.be * gate;
+
+  const bool no_long = a.wl == 0.f, no_prior = beb == 0.f;   // terms that are absent, masks included
+  // The entries of the step before (long, short, fused; -inf past the vocabulary and the call) are
+  // folded while the matrix cores work on this one.
+  float x[4], s[4], f[4];
+  int vp = 0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = s[e] = f[e] = -INFINITY;
+  auto fold = [&]() {
+    push4(P.L, x);
+    push4(P.S, s);
+    push4(P.F, f);
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) y[e] = f[e];
+    if (SAMPLE) {
+      const uint4 w4 = philox_row(a.smp, b, a.j, vp);
+      y[0] += gumbel_from_word(w4.x);
+      y[1] += gumbel_from_word(w4.y);
+      y[2] += gumbel_from_word(w4.z);
+      y[3] += gumbel_from_word(w4.w);
+    }
+    // top two of the four, then of the lane: tiles come in falling order of their index when rev,
+    // where an equal value replaces the one before
+    float m1 = -INFINITY, m2 = -INFINITY;
+    int mi = 0x7fffffff;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      m2 = __builtin_amdgcn_fmed3f(y[e], m1, m2);
+      const bool above = y[e] > m1;
+      mi = above ? vp + e : mi;
+      m1 = above ? y[e] : m1;
+    }
+    const bool up = (m1 > P.t1) | (rev & (m1 == P.t1));
+    P.t2 = up ? fmaxf(P.t1, m2) : fmaxf(P.t2, m1);
+    P.i1 = up ? mi : P.i1;
+    P.t1 = up ? m1 : P.t1;
+  };
+  auto step = [&](int u, int i) {
+    const int t = T0 + (rev ? steps - 1 - i : i) * NSTR + str;
+    u32x4_t* buf = s_w + (PL::kBufs == 1 ? 0 : (i & 1) * NSTR * kTile);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const uint32_t row = __umul24(piece(q), recip) >> 18;
+      const int pc = piece(q) - (int)row * pr;
+      if (row < 16 * (MT == 1 ? 1 : NSTR))
+        buf[((MT == 1 ? str : 0) + (row >> 4)) * kTile + 16 * pc + ((row ^ pc) & 15)] = w[u][q];
+    }
+    const typename Four<LT>::type lcur = lg[u];
+    load_step(u, i + PD);
+    if (MT > 1) __syncthreads();
+    const u32x4_t* sb = buf + str * kTile;
+    uint4 A[KC];
+#pragma unroll
+    for (int c = 0; c < KC; ++c) {
+      const int pc = 4 * c + g;
+      const u32x4_t raw = sb[16 * pc + (n ^ (pc & 15))];
+      A[c] = make_uint4(raw.x, raw.y, raw.z, raw.w);
+    }
+    f32x4_t acc[SPL];
+#pragma unroll
+    for (int e = 0; e < SPL; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < KC; ++c)
+#pragma unroll
+      for (int e = SPL - 1; e >= 0; --e) acc[e] = O::mma(A[c], act[c][e], acc[e]);
+    fold();
+    // products and fold share the wave's issue slots
+    constexpr int kMfma = KC * (sizeof(WT) == 2 ? SPL : 4);
+    constexpr int kValu = ((SAMPLE ? 330 : 130) + kMfma - 1) / kMfma;
+#pragma unroll
+    for (int q = 0; q < kMfma; ++q) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // a matrix instruction
+      __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);     // vector instructions of the fold
+    }
+    vp = 16 * t + 4 * g;
+    Four<LT>::widen(lcur, x);
+    float4 pv = {0.f, 0.f, 0.f, 0.f};
+    if (staged) pv = *reinterpret_cast<const float4*>(s_prior + vp - 16 * T0);
+    else if (a.prior && 16 * t + 16 <= V) pv = Four<float>::load(a.prior + vp);
+    const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      s[e] = SPL == 3 ? (acc[SPL - 1][e] + acc[SPL / 2][e]) + acc[0][e] : acc[0][e];
+      f[e] = __builtin_fmaf(alb, s[e], no_long ? 0.f : a.wl * x[e]);
+      f[e] = __builtin_fmaf(-beb, no_prior ? 0.f : pe[e], f[e]);
+      if (SAMPLE) f[e] *= a.smp.inv_temp;
+    }
+    if (16 * t + 16 > V || t >= T1) {   // uniform: the last tile of the vocabulary, or none
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int v = vp + e;
+        const bool in = v < V && t < T1;
+        const int vc = min(v, V - 1);
+        x[e] = to_f32(lrow[vc]);
+        f[e] = __builtin_fmaf(alb, s[e], no_long ? 0.f : a.wl * x[e]);
+        if (a.prior) f[e] = minus_weighted(f[e], beb, a.prior[vc]);
+        if (SAMPLE) f[e] *= a.smp.inv_temp;
+        x[e] = in ? x[e] : -INFINITY;
+        s[e] = in ? s[e] : -INFINITY;
+        f[e] = in ? f[e] : -INFINITY;
+      }
+    }
+  };
+  for (int i = 0; i < steps; i += PD) {
+#pragma unroll
+    for (int u = 0; u < PD; ++u)
+      if (i + u < steps) step(u, i + u);
+  }
+  fold();
+
+  // merge: the four row groups of a wave, then the NSTR waves of a sequence tile through LDS
+  close_lse(P.L);
+  close_lse(P.S);
+  close_lse(P.F);
+  P = allred_partial(P, Perm4Rows{});
+  __syncthreads();
+  Partial* sp = reinterpret_cast<Partial*>(smem);   // [str][16 MT]
+  if (g == 0) sp[str * 16 * MT + 16 * mt + n] = P;
+  __syncthreads();
+  if (tid < 128) {   // 128 partials: whole waves
+    const int s = tid / NSTR;
+    const Partial Q = allred_partial(sp[(tid % NSTR) * 16 * MT + s], PermN<NSTR>{});
+    if (tid % NSTR == 0 && b0 + s < a.batch) {
+      const size_t o = (size_t)(b0 + s) * a.G + blockIdx.x;
+      a.keys[o] = step_key(Q.t1, Q.i1);
+      a.parts[o] = StepPart{Q.L.m, Q.L.s, Q.S.m, Q.S.s, Q.F.m, Q.F.s, Q.t2};
+    }
+  }
+  if (a.finish && blockIdx.y == 0) {   // uniform
+    __syncthreads();
+    for (int row = blockIdx.x; row < a.batch; row += a.G) finish_row(fin, row, sp);
+  }
+}
+
+// The dynamic LDS limit of a kernel is raised to the maximum once per device (a per-call
+// attribute change costs microseconds of host time).
+template <auto Kern>
+hipError_t raise_lds_limit(size_t lds) {
+  if (lds <= 64 * 1024) return hipSuccess;
+  static std::atomic<uint64_t> raised{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (!bit || !(raised.load(std::memory_order_acquire) & bit)) {
+    e = hipFuncSetAttribute((const void*)Kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kMaxLds - 1024));
+    if (e != hipSuccess) return e;
+    raised.fetch_or(bit, std::memory_order_acq_rel);
+  }
+  return hipSuccess;
+}
+
+inline size_t vocab_lds(int MT, int kc, int spl) {
+  return std::max((size_t)MT * kc * spl * 1024, (size_t)kSW * 16 * MT * sizeof(Partial));
+}
+
+template <typename WT, typename LT, int MT, int SPL, bool SAMPLE>
+hipError_t launch_vocab_any(const VocabArgs<WT, LT>& a, const FinishArgs& fin, int nkb, dim3 grid, hipStream_t st) {
+  auto kern = k_vocab_any<WT, LT, MT, 8, SPL, SAMPLE>;
+  const size_t lds = vocab_lds(MT, nkb * 8, SPL);
+  hipError_t e = raise_lds_limit<k_vocab_any<WT, LT, MT, 8, SPL, SAMPLE>>(lds);
+  if (e != hipSuccess) return e;
+  kern<<<grid, kST, lds, st>>>(a, fin, nkb);
+  return hipGetLastError();
+}
+
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE>
+hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
+  auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE>;
+  // the final merge takes 128 partials
+  const size_t lds = std::max({VocabPlan<MT, KC, SAMPLE>::kLds + (a.prior ? kPriorTiles * 64 : 0), VocabPlan<MT, KC, SAMPLE>::act(SPL),
+                               128 * sizeof(Partial)});
+  hipError_t e = raise_lds_limit<k_vocab<WT, LT, MT, KC, SPL, SAMPLE>>(lds);
+  if (e != hipSuccess) return e;
+  kern<<<grid, kST, lds, st>>>(a, fin);
+  return hipGetLastError();
+}
+
+template <typename WT, typename LT, int SPL, bool SAMPLE>
+hipError_t launch_vocab(const VocabArgs<WT, LT>& a, const FinishArgs& fin, hipStream_t st) {
+  constexpr int K1 = 128 / Op<WT>::KCH, K2 = 256 / Op<WT>::KCH;   // chunks of 128 and of 256 columns
+  const unsigned gx = (unsigned)a.G;
+  const int mt = (a.batch + 15) / 16;
+  if (a.r > 256 || a.long_only) {
+    const int nkb = (a.r + 8 * Op<WT>::KCH - 1) / (8 * Op<WT>::KCH);
+    return mt == 1 ? launch_vocab_any<WT, LT, 1, SPL, SAMPLE>(a, fin, nkb, dim3(gx, 1), st)
+                   : launch_vocab_any<WT, LT, 2, SPL, SAMPLE>(a, fin, nkb, dim3(gx, (unsigned)((mt + 1) / 2)), st);
+  }
+  // as many tiles of 16 sequences per workgroup as the call has, at most four: the weights are
+  // read once per workgroup row
+#define DLS_VOCAB(MT)                                                                                          return a.r <= 128 ? launch_vocab_k<WT, LT, MT, K1, SPL, SAMPLE>(a, fin, dim3(gx, (unsigned)((mt + MT - 1) / MT)), st)                     : launch_vocab_k<WT, LT, MT, K2, SPL, SAMPLE>(a, fin, dim3(gx, (unsigned)((mt + MT - 1) / MT)), st)
+  if (mt == 1) DLS_VOCAB(1);
+  if (mt == 2) DLS_VOCAB(2);
+  DLS_VOCAB(4);
+#undef DLS_VOCAB
+}
+
+}  // namespace
+
+// The launches of one block (WT: head type, LT: long-logit type), instantiated one pair and
+// decoding mode per translation unit.
+template <typename WT, typename LT, bool SAMPLE>
+hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
+  const dls_local_head& hd = a.head;
+  const int batch = a.batch, B = a.B, V = hd.V, H = hd.H, r = hd.r;
+  const bool markov = hd.kind == DLS_HEAD_MARKOV;
+  char* ws = a.ws;
+  float* hc = (float*)(ws + a.lay.off_h0);   // current state
+  float* hn = (float*)(ws + a.lay.off_h1);   // next state
+  float* rho = (float*)(ws + a.lay.off_rho);
+  const int G = a.lay.groups;
+  const size_t per = (size_t)batch * G;
+  uint64_t* keys = (uint64_t*)(ws + a.lay.off_part);
+  // a Markov head's launches read the partials of the position before while they write: two sets
+  StepPart* parts = (StepPart*)(keys + (markov ? 2 : 1) * per);
+  const bool literal = (a.f.flags & DLS_FIRST_ROW_LONG_ONLY) != 0;
+  hipError_t e;
+
+  auto al_of = [&](int j) { return a.alphas ? a.alphas[j] : a.f.alpha; };
+  auto set_of = [&](int j) { return markov ? (size_t)(j & 1) * per : (size_t)0; };
+  auto finish_of = [&](int j) {
+    FinishArgs f;
+    f.keys = keys + set_of(j);
+    f.parts = parts + set_of(j);
+    f.G = G;
+    f.j = j;
+    f.B = B;
+    f.batch = batch;
+    f.wl = a.f.w_long;
+    f.al = al_of(j);
+    f.long_only = literal && j == 0;
+    f.out_tokens = a.out_tokens;
+    f.out_stats = a.out_stats;
+    f.smp = a.smp;
+    f.unc = a.unc;
+    return f;
+  };
+  bool first_head_step = true;
+  for (int j = 0; j < B; ++j) {
+    const bool long_only = literal && j == 0;
+    TokenSource ts;
+    ts.keys = j ? keys + set_of(j - 1) : nullptr;
+    ts.last = a.last_token;
+    ts.G = G;
+    const FinishArgs fin = finish_of(j ? j - 1 : 0);
+    if (!long_only && !markov) {
+      GatesArgs<WT> ga;
+      ga.emb = (const WT*)hd.emb;
+      ga.w_ih = (const WT*)hd.w_ih;
+      ga.w_hh = (const WT*)hd.w_hh;
+      ga.d = hd.d;
+      ga.H = H;
+      ga.V = V;
+      ga.batch = batch;
+      ga.ts = ts;
+      ga.h_in = hc;
+      ga.h_zero = first_head_step;
+      ga.h_out = hn;
+      const unsigned gx = (unsigned)((H + kUnits - 1) / kUnits);
+      if (batch <= 16) k_gates<WT, 1><<<dim3(gx, 1), kST, 0, st>>>(ga);
+      else if (batch <= 32) k_gates<WT, 2><<<dim3(gx, 1), kST, 0, st>>>(ga);
+      else k_gates<WT, 4><<<dim3(gx, (unsigned)((batch + 63) / 64)), kST, 0, st>>>(ga);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      RankArgs<WT> ra;
+      ra.w_rank = (const WT*)hd.w_rank;
+      ra.H = H;
+      ra.r = r;
+      ra.batch = batch;
+      ra.tiles = ((r + 15) / 16) * ((batch + 15) / 16);
+      ra.h = hn;
+      ra.rho = rho;
+      k_rank<WT><<<(unsigned)(ra.tiles + (j ? batch : 0)), kST, 0, st>>>(ra, fin);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      std::swap(hc, hn);
+      first_head_step = false;
+    }
+    VocabArgs<WT, LT> va;
+    va.w_vocab = (const WT*)hd.w_vocab;
+    va.V = V;
+    va.r = r;
+    va.batch = batch;
+    va.G = G;
+    va.np = (V + kPairRows - 1) / kPairRows;
+    va.rho = rho;
+    va.e_m = markov ? (const WT*)hd.emb : nullptr;
+    va.ts = ts;
+    va.L = (const LT*)a.long_logits + (size_t)j * V;
+    va.bstride = (size_t)B * V;
+    va.prior = a.prior;
+    va.wl = a.f.w_long;
+    va.al = al_of(j);
+    va.be = a.prior ? (a.betas ? a.betas[j] : a.f.beta) : 0.f;
+    va.long_only = long_only;
+    va.j = j;
+    va.B = B;
+    va.smp = a.smp;
+    va.unc = a.unc;
+    va.keys = keys + set_of(j);
+    va.parts = parts + set_of(j);
+    va.finish = markov && j;
+    e = markov ? launch_vocab<WT, LT, 1, SAMPLE>(va, fin, st) : launch_vocab<WT, LT, Op<WT>::SPL, SAMPLE>(va, fin, st);
+    if (e != hipSuccess) return e;
+  }
+  k_finish<<<batch, kST, 0, st>>>(finish_of(B - 1));
+  return hipGetLastError();
+}
+
+}  // namespace dls

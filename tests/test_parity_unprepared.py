@@ -1,0 +1,103 @@
+"""Heads drafted with as they are, at the sizes where the per-position kernels change their ways:
+operand tiles of 16 rows and 16 sequences, chunks of 32 (bf16) or 16 (float32) columns, five hidden units
+per workgroup, the vocabulary slice of a workgroup, the register form (r <= 256) and the LDS form above,
+one, two, four and more tiles of sequences, and the single-workgroup form of small heads.  Tokens and
+statistics against the oracle, and statistics within 2e-4 absolute: the logits here stay below about 100,
+float32 products and sums keep about 1e-6 relative."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import dels_oracle as O
+from paper_2607_07409_amd import binding as B
+from paper_2607_07409_amd import workloads as W
+from parity_util import check_draft
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # V, d, H, r, B, batch, dtype, long dtype, T, prior, literal, markov
+    (1, 8, 8, 8, 2, 1, "bf16", "bf16", 0.0, False, False, False),
+    (15, 8, 8, 8, 3, 17, "f32", "f32", 0.0, True, True, False),
+    (1024, 64, 64, 64, 4, 1, "f32", "f32", 0.0, True, False, False),
+    (2049, 72, 40, 88, 5, 3, "bf16", "f32", 0.7, True, False, False),
+    (1031, 0, 0, 128, 33, 5, "bf16", "bf16", 0.0, False, True, True),
+    (7000, 136, 264, 96, 4, 6, "f32", "f32", 0.0, True, False, False),
+    (30011, 1000, 264, 256, 4, 1, "bf16", "bf16", 0.0, False, False, False),
+    (30011, 264, 1024, 136, 3, 16, "bf16", "bf16", 1.0, True, False, False),
+    (20480, 520, 304, 128, 4, 17, "bf16", "f32", 0.0, True, True, False),
+    (33001, 4104, 72, 248, 3, 32, "bf16", "bf16", 0.0, False, False, False),
+    (16403, 256, 512, 256, 3, 33, "bf16", "bf16", 0.7, True, False, False),
+    (16400, 256, 512, 256, 4, 64, "f32", "bf16", 0.0, False, False, False),
+    (9001, 64, 136, 200, 3, 65, "bf16", "bf16", 0.0, True, False, False),
+    (5003, 128, 128, 512, 4, 20, "bf16", "bf16", 1.0, True, False, False),
+    (4099, 128, 128, 264, 3, 7, "f32", "f32", 0.0, True, True, False),
+    (20011, 0, 0, 256, 4, 24, "bf16", "bf16", 0.0, True, False, True),
+    (9973, 0, 0, 120, 5, 9, "f32", "f32", 0.7, False, True, True),
+    (8200, 0, 0, 264, 4, 50, "bf16", "bf16", 0.0, True, False, True),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_unprepared_edges(case):
+    V, d, H, r, Bk, batch, dt, ldt, T, with_prior, literal, markov = CASES[case]
+    print(CASES[case], flush=True)
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=V, d=max(d, 8), H=max(H, 8), r=r, B=Bk, batch=batch, dtype=dt, seed=900 + case)
+    if markov:
+        em, wm = W.make_markov_head(V, r, dt, 900 + case, scale=math.sqrt(3.0 / math.sqrt(r)))
+        head = B.LocalHead.markov_from_weights(em, wm)
+        oracle = O.MarkovHead(np.asarray(em, np.float64), np.asarray(wm, np.float64))
+    else:
+        hw = W.make_head(wl, "stress")
+        head, oracle = B.LocalHead.from_weights(hw), O.RnnHead.from_weights(hw)
+    long_h = W.make_long_logits(wl.with_(dtype=ldt))
+    last = W.make_last_token(wl)
+    prior = W.make_zipf_log_prior(V, 900 + case) if with_prior else None
+    al = [0.5 + 0.05 * j for j in range(Bk)]
+    be = [0.3 + 0.02 * j for j in range(Bk)] if with_prior else 0.0
+    lt = B.as_tensor(long_h)
+    assert head.path(batch, Bk, lt.dtype, with_prior) == 0
+    ws = B.draft_workspace(head, batch, Bk)
+    args = (head, lt, torch.from_numpy(np.asarray(last, np.int32)).cuda(),
+            None if prior is None else torch.from_numpy(np.ascontiguousarray(prior, np.float32)).cuda(), 1.0, al, be)
+    kw = dict(first_row_long_only=literal, workspace=ws, temperature=T, seed=77)
+    tok, st = B.draft_block(*args, **kw)
+    tok, st = tok.clone(), st.clone()
+    again = B.draft_block(*args, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(tok, again[0]) and torch.equal(st.view(torch.int32), again[1].view(torch.int32))
+    rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, prior, 1.0, al, be, literal,
+                      temperature=T, seed=77)
+    print(rep["near_ties"], rep["errs"])
+    assert all(e < 2e-4 for e in rep["errs"].values()), rep["errs"]
+
+
+@pytest.mark.parametrize("V,r,batch", [(1024, 64, 2), (20011, 128, 20), (9001, 264, 5)])
+def test_unprepared_masks_and_ties(V, r, batch):
+    """-inf and lowest-value masks, a row without a finite entry, exact ties (lowest index, on positions that
+    run through the vocabulary forwards and backwards) and a NaN logit, which may not hide from its row."""
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=V, d=64, H=64, r=r, B=4, batch=batch, dtype="bf16", seed=7)
+    hw = W.make_head(wl, "stress")
+    head, oracle = B.LocalHead.from_weights(hw), O.RnnHead.from_weights(hw)
+    long_h = np.asarray(W.make_long_logits(wl), np.float32).copy()
+    long_h[0, 0, ::2] = -np.inf
+    long_h[0, 1, 1::3] = np.float32(-3.0e38)
+    long_h[1, 2, :] = -np.inf
+    for j in range(4):
+        long_h[1, j, [V - 1, V // 2, 5]] = 200.0 if j != 2 else -np.inf
+    last = W.make_last_token(wl)
+    lt = torch.from_numpy(long_h).cuda()
+    run = lambda al: B.draft_block(head, lt, torch.from_numpy(np.asarray(last, np.int32)).cuda(), None, 1.0, al, 0.0)
+    tok, st = run(0.5)
+    # sequence 1 holds the row without a finite entry, whose statistics are infinite
+    rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, None, 1.0, 0.5, 0.0,
+                      sequences=[b for b in range(batch) if b != 1])
+    print(rep["near_ties"], rep["errs"])
+    tok0, _ = run(0.0)   # no short term: the ties are exact
+    assert tok0[1].tolist() == [5, 5, 0, 5]
+    long_h[0, 2, V // 3] = np.nan
+    lt.copy_(torch.from_numpy(long_h))
+    _, st = run(0.5)
+    assert torch.isnan(st[0, 2, 3]) and torch.isnan(st[0, 2, 5]) and torch.isfinite(st[0, :2, 3]).all()
