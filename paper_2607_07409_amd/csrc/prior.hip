@@ -46,33 +46,52 @@ __global__ __launch_bounds__(kCT) void k_count_sliced(const int32_t* __restrict_
   const int64_t lo = (int64_t)blockIdx.x * per;
   const int64_t hi = lo + per < n ? lo + per : n;
   uint32_t valid = 0;
-  int64_t i = lo + threadIdx.x;
-  // eight independent loads in flight per thread; ids are compared as unsigned offsets from
-  // the slice start, so negative ids and ids past V fall outside every slice
-  for (; i + 7 * kCT < hi; i += 8 * kCT) {
-    int t[8];
+  // ids are compared as unsigned offsets from the slice start, so negative ids and ids past V fall
+  // outside every slice; each slice counts its own tokens
+  auto count = [&](int t) {
+    const uint32_t u = (uint32_t)t - (uint32_t)v0;
+    if (u < (uint32_t)nv) {
+      atomicAdd(&s_hist[u], 1u);
+      ++valid;
+    }
+  };
+  const int64_t q0 = min(hi, lo + (int64_t)(((16u - ((uint32_t)(uintptr_t)(tokens + lo) & 15u)) & 15u) / 4u));
+  const int64_t nq = (hi - q0) / 4;   // whole 16-byte quads
+  if (threadIdx.x < q0 - lo) count(tokens[lo + threadIdx.x]);
+  if (threadIdx.x < hi - q0 - 4 * nq) count(tokens[q0 + 4 * nq + threadIdx.x]);
+  // 16-byte loads, kQ quads per thread, the next kQ on their way while these are counted (indices past
+  // the range clamped: loaded, not counted).  20 M Zipf(1.1) tokens over 151,936 ids: 91.1 -> 86.3 us
+  // against 4-byte loads, eight in flight, so the loads are not what bounds the count.
+  constexpr int kQ = 4;
+  const int4* qt = reinterpret_cast<const int4*>(tokens + q0);
+  if (nq > 0) {
+    int4 cur[kQ];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) t[k] = tokens[i + k * kCT];
+    for (int k = 0; k < kQ; ++k) cur[k] = qt[min((int64_t)threadIdx.x + k * kCT, nq - 1)];
+    for (int64_t i = threadIdx.x; i < nq; i += kQ * kCT) {
+      int4 nxt[kQ];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t u = (uint32_t)t[k] - (uint32_t)v0;
-      if (u < (uint32_t)nv) atomicAdd(&s_hist[u], 1u);
-      valid += (uint32_t)t[k] < (uint32_t)V;
+      for (int k = 0; k < kQ; ++k) nxt[k] = qt[min(i + (kQ + k) * kCT, nq - 1)];
+#pragma unroll
+      for (int k = 0; k < kQ; ++k) {
+        if (i + k * kCT < nq) {
+          count(cur[k].x);
+          count(cur[k].y);
+          count(cur[k].z);
+          count(cur[k].w);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < kQ; ++k) cur[k] = nxt[k];
     }
   }
-  for (; i < hi; i += kCT) {
-    const int t = tokens[i];
-    const uint32_t u = (uint32_t)t - (uint32_t)v0;
-    if (u < (uint32_t)nv) atomicAdd(&s_hist[u], 1u);
-    valid += (uint32_t)t < (uint32_t)V;
-  }
-  if (blockIdx.y == 0) atomicAdd(&s_valid, valid);
+  atomicAdd(&s_valid, valid);
   __syncthreads();
   for (int j = threadIdx.x; j < nv; j += kCT) {
     const uint32_t c = s_hist[j];
     if (c) atomicAdd((unsigned long long*)&counts[v0 + j], (unsigned long long)c);
   }
-  if (blockIdx.y == 0 && threadIdx.x == 0 && s_valid) atomicAdd((unsigned long long*)&counts[V], (unsigned long long)s_valid);
+  if (threadIdx.x == 0 && s_valid) atomicAdd((unsigned long long*)&counts[V], (unsigned long long)s_valid);
 }
 
 // Counting over vocabularies too large for a few slices: each workgroup keeps a direct-mapped cache of (token, count) pairs in LDS and

@@ -82,3 +82,16 @@ def test_unigram_prior_feeds_combine():
     for i in range(6):
         r = O.combine_row(np.asarray(L[i]), np.asarray(S[i]), P, 1.0, 0.5, 1.0)
         assert tok[i].item() == r.token or r.gap < 2e-2
+
+
+@pytest.mark.parametrize("offset", [0, 1, 2, 3])
+@pytest.mark.parametrize("n", [1, 3, 4, 7, 4096 * 4 + 5, 300_001])
+def test_unigram_prior_stream_alignment(n, offset):
+    """Streams that start between 16-byte boundaries, shorter and longer than one round of loads."""
+    V = 50_021
+    t = torch.from_numpy(np.random.default_rng(n + offset).integers(-2, V + 2, n + offset).astype(np.int32)).cuda()[offset:]
+    _, counts = B.unigram_log_prior(t, V)
+    toks = t.cpu().numpy()
+    valid = toks[(toks >= 0) & (toks < V)]
+    got = counts.cpu().numpy()
+    assert np.array_equal(got[:V], np.bincount(valid, minlength=V)) and got[V] == valid.size
