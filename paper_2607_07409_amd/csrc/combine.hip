@@ -8,7 +8,8 @@
 // The workgroup merge is a fixed-order butterfly, so results are deterministic.
 // Without row statistics or scores only the running maximum of l and its index are
 // kept: the argmax needs no normaliser, and the kernel is then bound by HBM bandwidth.
-// With parts > 1 a second kernel merges the per-range partials of each row.
+// With parts > 1 a second kernel merges the per-range partials of each row (the score kernel itself
+// where score rows are wanted).
 #include "dels_internal.hpp"
 #include "stream_load.hpp"
 
@@ -232,19 +233,77 @@ __global__ __launch_bounds__(64) void k_combine_finalize(const Partial* __restri
                  norm_out ? norm_out + row : nullptr);
 }
 
-// c_v = l_v - (w_long * lse_long + alpha * lse_short), recomputing l_v exactly as above
+// c_v = l_v - (w_long * lse_long + alpha * lse_short), recomputing l_v exactly as above.  Rows split
+// into parts are finished here as well: every workgroup merges its row's partials for the
+// normaliser (in the order of k_combine_finalize) and the first one of a row writes its results, which
+// saves the launch between: [48, 32003] float32 with the prior 18.2 -> 17.3 us.
+// 16-byte pieces from the first aligned long logit on; the scores' own alignment is that of a float.
+struct __attribute__((packed, aligned(4))) Store4 { float v[4]; };
 template <typename T, bool PRIOR, bool WLONG>
 __global__ __launch_bounds__(kThreads) void k_combine_scores(const T* __restrict__ L, const T* __restrict__ S,
                                                              const float* __restrict__ prior, int V, float wl,
                                                              float al, float be, const float* __restrict__ norm,
+                                                             const Partial* __restrict__ parts_in, int parts,
+                                                             int32_t* __restrict__ out_token,
+                                                             dls_row_stats* __restrict__ out_stats,
                                                              float* __restrict__ scores) {
-  const int row = blockIdx.x;
+  constexpr int N = Chunk<T>::N;
+  const int row = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const T* Lr = L + (size_t)row * V;
   const T* Sr = S + (size_t)row * V;
   float* Cr = scores + (size_t)row * V;
-  const float nr = norm[row];
-  for (int v = blockIdx.y * kThreads + threadIdx.x; v < V; v += gridDim.y * kThreads)
+  const int h0 = head_elems(Lr, V);
+  const int nch = (V - h0) / N;
+  const int stride = gridDim.y * kThreads;
+  int c = blockIdx.y * kThreads + t;
+  // the first pieces are on their way while the partials are merged
+  uint4 ra, rb;
+  if (c < nch) {
+    ra = Chunk<T>::raw(Lr + h0 + (size_t)c * N);
+    rb = Chunk<T>::raw(Sr + h0 + (size_t)c * N);
+  }
+  float nr;
+  if (parts > 1) {
+    Partial P = partial_empty();
+    for (int i = lane; i < parts; i += 64) P = partial_merge(P, parts_in[(size_t)row * parts + i]);
+    P = allred_partial(P, WaveXor{});
+    int32_t tok;
+    dls_row_stats st;
+    finalize_row(P, wl, al, false, &tok, &st, &nr);
+    if (blockIdx.y == 0 && t == 0) {
+      out_token[row] = tok;
+      if (out_stats) out_stats[row] = st;
+    }
+  } else {
+    nr = norm[row];
+  }
+  auto one = [&](int v) {
     Cr[v] = fuse1<PRIOR, WLONG>(to_f32(Lr[v]), to_f32(Sr[v]), PRIOR ? prior[v] : 0.f, wl, al, be) - nr;
+  };
+  if (blockIdx.y == 0) {
+    const int tail0 = h0 + nch * N;
+    if (t < h0) one(t);
+    if (t < V - tail0) one(tail0 + t);
+  }
+  while (c < nch) {
+    float a[N], b[N];
+    Chunk<T>::widen(ra, a);
+    Chunk<T>::widen(rb, b);
+    const int v0 = h0 + c * N;
+    c += stride;
+    if (c < nch) {
+      ra = Chunk<T>::raw(Lr + h0 + (size_t)c * N);
+      rb = Chunk<T>::raw(Sr + h0 + (size_t)c * N);
+    }
+#pragma unroll
+    for (int q = 0; q < N / 4; ++q) {
+      Store4 o;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        o.v[i] = fuse1<PRIOR, WLONG>(a[4 * q + i], b[4 * q + i], PRIOR ? prior[v0 + 4 * q + i] : 0.f, wl, al, be) - nr;
+      *reinterpret_cast<Store4*>(Cr + v0 + 4 * q) = o;
+    }
+  }
 }
 
 template <typename T, bool PRIOR, bool WLONG>
@@ -263,15 +322,18 @@ hipError_t launch_combine_t(const CombineArgs& a, hipStream_t st) {
                                                         norm);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (parts > 1) {
+  if (parts > 1 && !a.out_scores) {
     k_combine_finalize<<<(unsigned)a.rows, 64, 0, st>>>(a.partials, parts, a.wl, a.al, a.out_token,
                                                          a.out_stats, norm);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (a.out_scores) {
-    dim3 g2((unsigned)a.rows, (unsigned)std::min<int64_t>((a.V + kThreads - 1) / kThreads, 64));
-    k_combine_scores<T, PRIOR, WLONG><<<g2, kThreads, 0, st>>>((const T*)a.long_logits, (const T*)a.short_logits,
-                                                        a.prior, a.V, a.wl, a.al, a.be, a.norm, a.out_scores);
+    // about eight workgroups per CU, none without a piece for each of its threads
+    const int64_t per_row = std::max<int64_t>(1, std::min<int64_t>(a.V / (Chunk<T>::N * kThreads), (2048 + a.rows - 1) / a.rows));
+    dim3 g2((unsigned)a.rows, (unsigned)per_row);
+    k_combine_scores<T, PRIOR, WLONG><<<g2, kThreads, 0, st>>>(
+        (const T*)a.long_logits, (const T*)a.short_logits, a.prior, a.V, a.wl, a.al, a.be, a.norm, a.partials, parts,
+        a.out_token, a.out_stats, a.out_scores);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;

@@ -213,3 +213,24 @@ def test_combine_tokens_only_ties_and_masks():
     torch.cuda.synchronize()
     Lm = np.where(np.isneginf(L), -np.inf, L)
     assert np.array_equal(t.cpu().numpy(), np.argmax(Lm, axis=1))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,V", [(1, 4097), (48, 12290), (3, 32003), (2, 4096), (300, 4101)])
+def test_combine_scores_of_split_rows(rows, V, dtype):
+    """Score rows whose kernel also merges the row's parts (and whole rows): tokens and statistics are
+    those of the call without scores bit for bit, and every score is within float32 rounding of the
+    oracle's (values below 32 in magnitude: 1e-4)."""
+    L = W.make_logit_rows(rows, V, dtype, 50 + V, "onehot", 3.0, purpose=20)
+    S = W.make_logit_rows(rows, V, dtype, 50 + V, "normal", 2.0, purpose=21)
+    P = W.make_zipf_log_prior(V, 50)
+    lt, st, pt = B.as_tensor(L), B.as_tensor(S), torch.from_numpy(np.ascontiguousarray(P, np.float32)).cuda()
+    plain = B.combine_logits(lt, st, pt, 1.0, 0.3, 0.3, want_stats=True)
+    both = B.combine_logits(lt, st, pt, 1.0, 0.3, 0.3, want_stats=True, want_scores=True)
+    bare = B.combine_logits(lt, st, pt, 1.0, 0.3, 0.3, want_stats=False, want_scores=True)
+    torch.cuda.synchronize()
+    assert torch.equal(plain[0], both[0]) and torch.equal(plain[1], both[1])
+    assert torch.equal(bare[0], both[0]) and torch.equal(bare[2], both[2])
+    for i in sorted({0, rows // 2, rows - 1}):
+        ref = O.combine_row(L[i], S[i], P, 1.0, 0.3, 0.3, want_scores=True).scores
+        assert np.max(np.abs(both[2][i].cpu().numpy() - ref)) < 1e-4
