@@ -184,11 +184,12 @@ dls_status dls_combine_logits(const void *long_logits, const void *short_logits,
  * One draft block per sequence (Algorithm 1, the decoding loop).
  * Two implementations share this entry point.  With head->prepared set and a supported
  * shape (bf16 head, H/16 <= number of CUs, r divisible by H/16 with at most 16 rank rows
- * per group, and the per-CU share of W_vocab fitting in AGPRs + LDS) one persistent kernel
- * keeps the head weights on chip for the whole block, for at most 64 sequences per launch
- * (a larger batch runs as consecutive launches of 64 on the same workspace and stream;
- * sampling keys its noise by each sequence's index in the whole call, so the split does not
- * change a draw); otherwise each position is a sequence of kernel launches.
+ * per group, and the per-CU share of W_vocab fitting in AGPRs + LDS) a call of up to 32
+ * sequences runs in one persistent kernel that keeps the head weights on chip for the whole
+ * block, and a larger one as a chain of launches per position that reads the prepared form;
+ * otherwise the chain reads the head as it is (a head of at most 1 MiB of weights drafts the
+ * whole block in one launch).  Sampling keys its noise by each sequence's index in the call,
+ * so the route does not change a draw.
  * dls_draft_block_path tells which is used.
  * The workspace must be zero-filled before its first use; the library keeps it
  * consistent afterwards.  A persistent call that fails sets the workspace's error word
@@ -211,7 +212,8 @@ dls_status dls_combine_logits(const void *long_logits, const void *short_logits,
  * Limits: 1 <= batch <= 256, 1 <= B <= 64 (0 is a no-op), the head limits above,
  * long_dtype F32 or BF16. */
 size_t dls_draft_block_workspace_size(const dls_local_head *head, int32_t batch, int32_t B);
-/* 1: the persistent kernel would be used for these arguments, 0: per-position launches,
+/* 1: the prepared form would be used for these arguments (the persistent kernel, or above 32
+ * sequences the launches per position), 0: launches that read the head as it is,
  * negative: the arguments are invalid.  Needs the device (it counts its CUs). */
 int dls_draft_block_path(const dls_local_head *head, int32_t batch, int32_t B, dls_dtype long_dtype,
                          int has_prior);

@@ -406,9 +406,28 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
     hipError_t e = dls::launch_uncertainty(ua, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "draft_block_adaptive uncertainty launch");
   }
+  dls::DraftArgs a;
+  a.head = ch;
+  a.long_logits = long_logits;
+  a.long_dtype = long_dtype;
+  a.last_token = last_token;
+  a.prior = prior;
+  a.batch = batch;
+  a.B = B;
+  a.f = fusion;
+  if (!prior) a.f.beta = 0.f;
+  a.out_tokens = out_tokens;
+  a.out_stats = out_stats;
+  a.ws = (char*)workspace + pw.total;
+  a.lay = dls::draft_layout(ch, batch, B);
+  a.alphas = alphas;
+  a.betas = betas;
+  a.smp = smp;
+  a.unc = out_unc;
   if (head->prepared) {
-    // A call of more than kMaxBatch sequences runs as consecutive launches of at most kMaxBatch
-    // sequences each, on the same workspace and stream; every launch's plan is checked first.
+    // The prepared form is used where the persistent kernel's plan holds for the call, kMaxBatch
+    // sequences at a time: by that kernel up to kPersistBatch sequences, by the launches per
+    // position above.
     const int nfull = std::min<int32_t>(batch, dls::kMaxBatch);
     const int nlast = batch - (batch - 1) / dls::kMaxBatch * dls::kMaxBatch;   // the last launch's sequences
     const dls::PersistPlan pl = dls::persist_plan(ch, nfull, B, long_dtype, prior != nullptr, persist_groups(cus));
@@ -419,17 +438,30 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
       const dls::PreparedLayout PL = dls::prepared_layout(ch);
       const char* pp = (const char*)head->prepared;
       char* ws = (char*)workspace;
+      dls::PreparedHeader expect;
+      expect.magic = dls::kPreparedMagic;
+      expect.V = ch.V;
+      expect.d = ch.d;
+      expect.H = ch.H;
+      expect.r = ch.r;
+      expect.emb = ch.emb;
+      expect.w_ih = ch.w_ih;
+      expect.w_hh = ch.w_hh;
+      expect.w_vocab = ch.w_vocab;
+      if (batch > dls::kPersistBatch) {
+        a.T = ch.kind == DLS_HEAD_MARKOV ? nullptr : (const float*)(pp + PL.off_T);
+        a.wv = (const uint4*)(pp + PL.off_wv);
+        a.whh = (const uint4*)(pp + PL.off_whh);
+        a.prep = (const dls::PreparedHeader*)pp;
+        a.expect = &expect;
+        a.hdr = (uint32_t*)ws;
+        hipError_t e = dls::launch_draft(a, (hipStream_t)stream);
+        if (e != hipSuccess) return hip_fail(e, "draft_block prepared launch");
+        return DLS_OK;
+      }
       dls::PersistArgs pa;
       pa.prep = (const dls::PreparedHeader*)pp;
-      pa.expect.magic = dls::kPreparedMagic;
-      pa.expect.V = ch.V;
-      pa.expect.d = ch.d;
-      pa.expect.H = ch.H;
-      pa.expect.r = ch.r;
-      pa.expect.emb = ch.emb;
-      pa.expect.w_ih = ch.w_ih;
-      pa.expect.w_hh = ch.w_hh;
-      pa.expect.w_vocab = ch.w_vocab;
+      pa.expect = expect;
       pa.T = (const float*)(pp + PL.off_T);
       pa.wv = (const uint4*)(pp + PL.off_wv);
       pa.whh = (const uint4*)(pp + PL.off_whh);
@@ -451,57 +483,33 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
       // one copy of the wide h hand-off words: replicas (each GRU workgroup reading its own) cost
       // more in publish stores on the critical path than they saved in reads
       pa.hrep = 1;
-      const size_t lsz = long_dtype == DLS_BF16 ? 2 : 4;
-      for (int b0 = 0; b0 < batch; b0 += dls::kMaxBatch) {
-        const int nb = std::min<int32_t>(dls::kMaxBatch, batch - b0);
-        const dls::PersistPlan& plc = nb == nfull ? pl : pl_last;
-        const dls::PersistWorkspace pwc = dls::persist_workspace(ch, nb, B);
-        pa.NT = plc.NT;
-        pa.NG = plc.NG;
-        pa.rpg = plc.rpg;
-        pa.cap_a = plc.cap_a;
-        pa.gcap = plc.gcap;
-        pa.rows_max = plc.rows_max;
-        pa.lds_region_a = plc.lds_region_a;
-        pa.batch = nb;
-        pa.L = (const char*)long_logits + (size_t)b0 * B * ch.V * lsz;
-        pa.last = last_token ? last_token + b0 : nullptr;
-        pa.smp = smp;
-        pa.smp.b0 = (uint32_t)b0;   // the noise of a sequence is keyed by its index in the call
-        pa.unc = out_unc ? out_unc + (size_t)b0 * B : nullptr;
-        pa.out_tokens = out_tokens + (size_t)b0 * B;
-        pa.out_stats = out_stats ? out_stats + (size_t)b0 * B : nullptr;
-        pa.keys = (uint64_t*)(ws + pwc.off_keys);
-        pa.hbuf = (uint64_t*)(ws + pwc.off_h);
-        pa.h32 = (uint32_t*)(ws + pwc.off_h32);
-        pa.rbuf = (uint64_t*)(ws + pwc.off_rho);
-        pa.stats = (uint64_t*)(ws + pwc.off_stats);
-        pa.tokw = (uint64_t*)(ws + pwc.off_tokw);
-        hipError_t e = dls::launch_persistent(pa, plc, long_dtype, (hipStream_t)stream);
-        if (e != hipSuccess) return hip_fail(e, "draft_block persistent launch");
-      }
+      const dls::PersistWorkspace pwc = dls::persist_workspace(ch, batch, B);
+      pa.NT = pl.NT;
+      pa.NG = pl.NG;
+      pa.rpg = pl.rpg;
+      pa.cap_a = pl.cap_a;
+      pa.gcap = pl.gcap;
+      pa.rows_max = pl.rows_max;
+      pa.lds_region_a = pl.lds_region_a;
+      pa.batch = batch;
+      pa.L = long_logits;
+      pa.last = last_token;
+      pa.smp = smp;
+      pa.unc = out_unc;
+      pa.out_tokens = out_tokens;
+      pa.out_stats = out_stats;
+      pa.keys = (uint64_t*)(ws + pwc.off_keys);
+      pa.hbuf = (uint64_t*)(ws + pwc.off_h);
+      pa.h32 = (uint32_t*)(ws + pwc.off_h32);
+      pa.rbuf = (uint64_t*)(ws + pwc.off_rho);
+      pa.stats = (uint64_t*)(ws + pwc.off_stats);
+      pa.tokw = (uint64_t*)(ws + pwc.off_tokw);
+      hipError_t e = dls::launch_persistent(pa, pl, long_dtype, (hipStream_t)stream);
+      if (e != hipSuccess) return hip_fail(e, "draft_block persistent launch");
       return DLS_OK;
     }
   }
 
-  dls::DraftArgs a;
-  a.head = ch;
-  a.long_logits = long_logits;
-  a.long_dtype = long_dtype;
-  a.last_token = last_token;
-  a.prior = prior;
-  a.batch = batch;
-  a.B = B;
-  a.f = fusion;
-  if (!prior) a.f.beta = 0.f;
-  a.out_tokens = out_tokens;
-  a.out_stats = out_stats;
-  a.ws = (char*)workspace + pw.total;
-  a.lay = dls::draft_layout(ch, batch, B);
-  a.alphas = alphas;
-  a.betas = betas;
-  a.smp = smp;
-  a.unc = out_unc;
   hipError_t e = dls::launch_draft(a, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "draft_block launch");
   return DLS_OK;

@@ -79,6 +79,7 @@ struct DraftLayout {
 };
 DraftLayout draft_layout(const dls_local_head& h, int32_t batch, int32_t B);
 
+struct PreparedHeader;
 struct DraftArgs {
   dls_local_head head;
   const void* long_logits;
@@ -95,6 +96,13 @@ struct DraftArgs {
   const float* betas;        // [B] host, or NULL (f.beta)
   Sampler smp;               // temperature sampling (smp.inv_temp = 0: greedy)
   const dls_row_uncertainty* unc;   // [batch, B] adaptive-fusion gates, or NULL (gate 1)
+  // a prepared head (NULL otherwise): its regions, the header to check against what it must hold, and
+  // the workspace header with the error word
+  const float* T = nullptr;
+  const uint4 *wv = nullptr, *whh = nullptr;
+  const PreparedHeader* prep = nullptr;
+  const PreparedHeader* expect = nullptr;   // host
+  uint32_t* hdr = nullptr;
 };
 hipError_t launch_draft(const DraftArgs& a, hipStream_t st);
 bool small_head(const dls_local_head& h, int32_t B);   // drafted by one workgroup per sequence
@@ -108,7 +116,12 @@ hipError_t launch_unigram_prior(const int32_t* tokens, int64_t n, int32_t V, flo
 // ------------------------------------------------------------------------------------------
 // prepared heads and the persistent drafting kernel
 // ------------------------------------------------------------------------------------------
-constexpr int kMaxBatch = 64;              // sequences per call on the persistent path
+constexpr int kMaxBatch = 64;              // sequences of one plan of the persistent kernel
+// Prepared heads of more sequences than this are drafted by the launches per position.  The persistent
+// kernel's position costs one chain of hand-offs per 16 sequences, the launches' little more for 64
+// than for 16: at V = 151,936, H = 1,024, r = 256 a block of 64 sequences takes 679 us against 993, one
+// of 40 sampled sequences 770 against 871; at 32 both take about 545.
+constexpr int kPersistBatch = 32;
 constexpr int kMaxG = 256;                 // workgroups (one per CU of a gfx950)
 constexpr size_t kMaxLds = 160 * 1024;     // LDS per CU on gfx950
 constexpr int kNarrowBatch = 4;            // the persistent kernel's narrow form: at most 4 sequences

@@ -11,7 +11,7 @@
 // device and no launch waits for another one beyond the order of the stream.
 //
 // All products run on the matrix cores, 16 weight rows by 16 sequences at a time, with float32
-// accuracy (V = 151,936, d = 4,096, H = 1,024, r = 256, 32 sequences, 16 positions in bf16: 763 us a
+// accuracy (V = 151,936, d = 4,096, H = 1,024, r = 256, 32 sequences, 16 positions in bf16: 749 us a
 // block; one wave per weight row with vector instructions, four sequences at a time, took 10.5 ms,
 // and its error against float64 was larger): a float32 activation is split exactly into three bf16 values of 8 significant bits
 // (bf16 heads, v_mfma_f32_16x16x32_bf16), or multiplied as it is (float32 heads,
@@ -235,8 +235,17 @@ struct FinishArgs {
   dls_row_stats* out_stats;
   Sampler smp;
   const dls_row_uncertainty* unc;
+  const uint32_t* hdr;   // header of the workspace (prepared heads): a set error word gives sentinels
 };
 __device__ __forceinline__ void finish_row(const FinishArgs& f, int b, Partial* sh) {
+  if (f.hdr && f.hdr[1] != 0u) {   // uniform
+    if (threadIdx.x == 0) {
+      const float nan = __builtin_nanf("");
+      f.out_tokens[(size_t)b * f.B + f.j] = -1;
+      if (f.out_stats) f.out_stats[(size_t)b * f.B + f.j] = dls_row_stats{nan, nan, nan, nan, nan, nan};
+    }
+    return;
+  }
   Partial P = partial_empty();
   for (int i = threadIdx.x; i < f.G; i += kST) {
     const uint64_t k = f.keys[(size_t)b * f.G + i];
@@ -394,6 +403,103 @@ __global__ __launch_bounds__(kST, 2) void k_gates(GatesArgs<WT> a) {
   }
 }
 
+// A prepared buffer of another head sets the error word (an earlier one stays).
+__global__ void k_check_prepared(const PreparedHeader* prep, PreparedHeader ex, uint32_t* hdr) {
+  const bool same = prep->magic == ex.magic && prep->V == ex.V && prep->d == ex.d && prep->H == ex.H && prep->r == ex.r &&
+                    prep->emb == ex.emb && prep->w_ih == ex.w_ih && prep->w_hh == ex.w_hh && prep->w_vocab == ex.w_vocab;
+  if (!same) hdr[1] = kErrPrepared;
+}
+
+// GRU cell of a prepared head: the input products come from the folded table, W_hh in operand
+// order.  A workgroup owns 16 hidden units (three operand tiles) and 16 sequences; the waves take
+// an eighth of the columns each.  Bound by latency: the keys of the position before, the rows of T
+// from HBM; W_hh and h are on their way meanwhile.
+struct FoldedArgs {
+  const float* T;
+  const uint4* whh;
+  int H, V, batch;
+  TokenSource ts;
+  const float* h_in;
+  int h_zero;
+  float* h_out;
+};
+__global__ __launch_bounds__(kST, 2) void k_gates_folded(FoldedArgs a) {
+  using O = Op<bf16_t>;
+  constexpr int NB = 4;   // chunks in flight
+  __shared__ int s_tok[16];
+  __shared__ f32x4_t red[kSW][3][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = lane & 15, g = lane >> 4;
+  const int b0 = blockIdx.y * 16, H = a.H, nc = H / 32;
+  TokenKeys<2> tk;
+  load_keys(a.ts, b0, a.batch, wave, lane, tk);
+  asm volatile("" ::: "memory");
+  const int c0 = nc * wave / kSW, c1 = nc * (wave + 1) / kSW;
+  const u32x4_t* wp = reinterpret_cast<const u32x4_t*>(a.whh) + (size_t)blockIdx.x * 3 * nc * 64 + lane;
+  const float* hr = a.h_in + (size_t)min(b0 + n, a.batch - 1) * H + 8 * g;
+  f32x4_t acc[3];
+  acc[0] = acc[1] = acc[2] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  u32x4_t w[3][NB];
+  f32x4_t x[NB][2];
+  auto load = [&](int c) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      const int ci = min(c + i, nc - 1);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) w[q][i] = wp[((size_t)q * nc + ci) * 64];
+      x[i][0] = *reinterpret_cast<const f32x4_t*>(hr + 32 * ci);
+      x[i][1] = *reinterpret_cast<const f32x4_t*>(hr + 32 * ci + 4);
+    }
+  };
+  if (!a.h_zero) load(c0);
+  const int u = tid & 15, s = tid >> 4, b = b0 + s, unit = blockIdx.x * 16 + u;   // tid < 256
+  const bool mine = tid < 256 && b < a.batch;
+  const float hp = mine && !a.h_zero ? a.h_in[(size_t)b * H + unit] : 0.f;
+  asm volatile("" ::: "memory");
+  merge_keys(tk, a.V, wave, lane, s_tok);
+  __syncthreads();
+  float gi[3] = {0.f, 0.f, 0.f};
+  if (mine) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) gi[q] = a.T[(size_t)s_tok[s] * 3 * H + q * H + unit];
+  }
+  if (!a.h_zero) {
+    for (int c = c0; c < c1; c += NB) {
+      if (c > c0) load(c);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        if (c + i < c1) {   // wave-uniform
+          const float4 v[2] = {make_float4(x[i][0].x, x[i][0].y, x[i][0].z, x[i][0].w),
+                               make_float4(x[i][1].x, x[i][1].y, x[i][1].z, x[i][1].w)};
+          uint4 sp[O::SPL];
+          act_split<bf16_t>(v, true, sp);
+#pragma unroll
+          for (int e = O::SPL - 1; e >= 0; --e)
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+              acc[q] = O::mma(make_uint4(w[q][i].x, w[q][i].y, w[q][i].z, w[q][i].w), sp[e], acc[q]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) red[wave][q][lane] = acc[q];
+  __syncthreads();
+  if (mine) {
+    const int l = 16 * (u >> 2) + s;
+    float gh[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      gh[q] = 0.f;
+#pragma unroll
+      for (int v = 0; v < kSW; ++v) gh[q] += red[v][q][l][u & 3];
+    }
+    const float rg = sigmoidf_(gi[0] + gh[0]), zg = sigmoidf_(gi[1] + gh[1]);
+    const float ng = tanhf_(gi[2] + rg * gh[2]);
+    a.h_out[(size_t)b * H + unit] = (1.f - zg) * ng + zg * hp;
+  }
+}
+
 // ----------------------------------------------------------------------------------
 // rho = SiLU(W_rank h), 16 rank rows by 16 sequences per workgroup (columns split over the
 // waves); the workgroups after them write the results of the position before (fin.batch of
@@ -447,6 +553,7 @@ __global__ __launch_bounds__(kST) void k_rank(RankArgs<WT> a, FinishArgs fin) {
 template <typename WT, typename LT>
 struct VocabArgs {
   const WT* w_vocab;
+  const uint4* wv;               // the same in operand order (a prepared head), or NULL
   int V, r, batch, G, np;        // np = ceil(V / kPairRows)
   const float* rho;              // RNN head
   const WT* e_m;                 // Markov head (then ts holds the tokens)
@@ -809,14 +916,10 @@ template <> struct Four<float> {
     x[3] = v.w;
   }
 };
-__device__ __forceinline__ void push4(Lse& a, const float* x) {
-  lse_fold_fin<4>(a, x, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
-}
-
 constexpr int kPriorTiles = 128;   // tiles of prior entries a workgroup keeps in LDS (8 KB)
 template <int MT, int KC, bool SAMPLE>
 struct VocabPlan {
-  static constexpr int NSTR = kSW / MT;
+  static constexpr int NSTR = kSW / MT;                           // tiles per step
   static constexpr int NP = NSTR * KC / kSW;                      // 16-byte pieces per thread and step
   // as deep as the registers allow without spills (the noise of a sampled row takes some)
   static constexpr int PD = NP >= 16 ? 1 : NP >= 8 ? (SAMPLE ? 1 : 2) : NP >= 4 ? 3 : NP >= 2 ? 6 : 8;
@@ -826,7 +929,8 @@ struct VocabPlan {
   static constexpr size_t act(int spl) { return (size_t)MT * KC * spl * 1024; }
 };
 
-template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE>
+// PACKED: the weights are in operand order already (KC chunks a tile), else rows of r columns.
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED>
 __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArgs fin) {
   using O = Op<WT>;
   using PL = VocabPlan<MT, KC, SAMPLE>;
@@ -852,17 +956,19 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   const uint32_t recip = ((1u << 18) + (uint32_t)pr - 1) / (uint32_t)pr;
   static_assert(kST * NP <= 4096 || MT == 1, "pieces of a step");
   auto piece = [&](int q) { return MT == 1 ? q * 64 + lane : q * kST + tid; };
-  const int wbase = MT == 1 ? str * 16 * pr : 0;
-  const int last = (V - 1) * pr + pr - 1;
+  const int tile_pieces = PACKED ? kTile : 16 * pr;
+  const int wbase = MT == 1 ? str * tile_pieces : 0;
+  const int last = PACKED ? (int)nt * kTile - 1 : (V - 1) * pr + pr - 1;
+  const u32x4_t* wsrc = PACKED ? reinterpret_cast<const u32x4_t*>(a.wv) : reinterpret_cast<const u32x4_t*>(a.w_vocab);
   u32x4_t w[PD][NP];
   typename Four<LT>::type lg[PD];
   auto load_step = [&](int u, int i) {
     if (i >= steps) return;   // uniform
     const int ii = rev ? steps - 1 - i : i;
-    const int first = (T0 + ii * NSTR) * 16 * pr;
+    const int first = (T0 + ii * NSTR) * tile_pieces;
 #pragma unroll
     for (int q = 0; q < NP; ++q)   // past the matrix: its last piece, for rows that are not folded
-      w[u][q] = *reinterpret_cast<const u32x4_t*>(a.w_vocab + (size_t)min(first + wbase + piece(q), last) * O::NP);
+      w[u][q] = wsrc[min(first + wbase + piece(q), last)];
     const int t = T0 + ii * NSTR + str;
     if (16 * t + 16 <= V) lg[u] = Four<LT>::load(lrow + 16 * t + 4 * g);
   };
@@ -873,7 +979,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   // The workgroup's slice of the prior goes to LDS with them.
   constexpr int NA = (MT * KC * 64 + kST - 1) / kST;
   float* s_prior = reinterpret_cast<float*>(smem + PL::kLds);
-  const bool staged = a.prior && T1 - T0 + NSTR <= kPriorTiles;   // also read by waves past the last tile
+  const bool staged = a.prior != nullptr;   // the slice fits: T1 - T0 + NSTR <= kPriorTiles
   float pv0[kPriorTiles * 16 / kST];
   if (staged) {
 #pragma unroll
@@ -951,18 +1057,34 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   P.L.m = P.S.m = P.F.m = kFinMin;
   const float gate = a.unc ? a.unc[(size_t)bc * a.B + a.j].gate : 1.f;
   const float alb = a.al * gate, beb = a.be * gate;
+  const bool no_prior = beb == 0.f;   // the term is absent, masks included
 
-  const bool no_long = a.wl == 0.f, no_prior = beb == 0.f;   // terms that are absent, masks included
   // The entries of the step before (long, short, fused; -inf past the vocabulary and the call) are
-  // folded while the matrix cores work on this one.
+  // folded while the matrix cores work on this one.  A log-sum-exp's reference need not be the
+  // maximum: it is moved when a value lies more than kLag above it (the sums stay below
+  // 2^24 exp(kLag), far from overflow), which takes the rescaling out of the fold.
+  constexpr float kLag = 40.f;
   float x[4], s[4], f[4];
   int vp = 0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) x[e] = s[e] = f[e] = -INFINITY;
+  float nl = -kFinMin * kLog2e, ns = nl, nf = nl;   // minus the references, base 2
+  auto max4 = [](const float* v) { return fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])); };
+  auto add4 = [](Lse& a, float neg, const float* v) {
+    const float e0 = fast_exp2(__builtin_fmaf(v[0], kLog2e, neg)), e1 = fast_exp2(__builtin_fmaf(v[1], kLog2e, neg));
+    const float e2 = fast_exp2(__builtin_fmaf(v[2], kLog2e, neg)), e3 = fast_exp2(__builtin_fmaf(v[3], kLog2e, neg));
+    a.s += (e0 + e1) + (e2 + e3);
+  };
+  auto move_ref = [](Lse& a, float& neg, float m) {   // to m where that is above the reference
+    const float mn = fmaxf(a.m, m);
+    a.s *= fast_exp2((a.m - mn) * kLog2e);
+    a.m = mn;
+    neg = -mn * kLog2e;
+  };
   auto fold = [&]() {
-    push4(P.L, x);
-    push4(P.S, s);
-    push4(P.F, f);
+    add4(P.L, nl, x);
+    add4(P.S, ns, s);
+    add4(P.F, nf, f);
     float y[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = f[e];
@@ -989,25 +1111,12 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
     P.i1 = up ? mi : P.i1;
     P.t1 = up ? m1 : P.t1;
   };
-  auto step = [&](int u, int i) {
-    const int t = T0 + (rev ? steps - 1 - i : i) * NSTR + str;
-    u32x4_t* buf = s_w + (PL::kBufs == 1 ? 0 : (i & 1) * NSTR * kTile);
-#pragma unroll
-    for (int q = 0; q < NP; ++q) {
-      const uint32_t row = __umul24(piece(q), recip) >> 18;
-      const int pc = piece(q) - (int)row * pr;
-      if (row < 16 * (MT == 1 ? 1 : NSTR))
-        buf[((MT == 1 ? str : 0) + (row >> 4)) * kTile + 16 * pc + ((row ^ pc) & 15)] = w[u][q];
-    }
-    const typename Four<LT>::type lcur = lg[u];
-    load_step(u, i + PD);
-    if (MT > 1) __syncthreads();
-    const u32x4_t* sb = buf + str * kTile;
+  auto tile = [&](int t, const u32x4_t* sb, typename Four<LT>::type lcur) {
     uint4 A[KC];
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
       const int pc = 4 * c + g;
-      const u32x4_t raw = sb[16 * pc + (n ^ (pc & 15))];
+      const u32x4_t raw = sb[PACKED ? c * 64 + lane : 16 * pc + (n ^ (pc & 15))];
       A[c] = make_uint4(raw.x, raw.y, raw.z, raw.w);
     }
     f32x4_t acc[SPL];
@@ -1018,26 +1127,32 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
 #pragma unroll
       for (int e = SPL - 1; e >= 0; --e) acc[e] = O::mma(A[c], act[c][e], acc[e]);
     fold();
-    // products and fold share the wave's issue slots
+    // Four sequence tiles: products and fold share the wave's issue slots (33.3 -> 30.2 us together with
+    // the lagging references).  With fewer the stream of weights is the bound, and the registers
+    // that the interleaving takes would spill.
     constexpr int kMfma = KC * (sizeof(WT) == 2 ? SPL : 4);
-    constexpr int kValu = ((SAMPLE ? 330 : 130) + kMfma - 1) / kMfma;
+    constexpr int kValu = ((SAMPLE ? 300 : 100) + kMfma - 1) / kMfma;
 #pragma unroll
-    for (int q = 0; q < kMfma; ++q) {
+    for (int q = 0; q < (MT == 4 ? kMfma : 0); ++q) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // a matrix instruction
       __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);     // vector instructions of the fold
     }
     vp = 16 * t + 4 * g;
     Four<LT>::widen(lcur, x);
-    float4 pv = {0.f, 0.f, 0.f, 0.f};
-    if (staged) pv = *reinterpret_cast<const float4*>(s_prior + vp - 16 * T0);
-    else if (a.prior && 16 * t + 16 <= V) pv = Four<float>::load(a.prior + vp);
-    const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       s[e] = SPL == 3 ? (acc[SPL - 1][e] + acc[SPL / 2][e]) + acc[0][e] : acc[0][e];
-      f[e] = __builtin_fmaf(alb, s[e], no_long ? 0.f : a.wl * x[e]);
-      f[e] = __builtin_fmaf(-beb, no_prior ? 0.f : pe[e], f[e]);
-      if (SAMPLE) f[e] *= a.smp.inv_temp;
+      f[e] = __builtin_fmaf(alb, s[e], a.wl * x[e]);
+    }
+    if (a.prior) {   // uniform
+      const float4 pv = *reinterpret_cast<const float4*>(s_prior + vp - 16 * T0);
+      const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = __builtin_fmaf(-beb, no_prior ? 0.f : pe[e], f[e]);
+    }
+    if (SAMPLE) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] *= a.smp.inv_temp;
     }
     if (16 * t + 16 > V || t >= T1) {   // uniform: the last tile of the vocabulary, or none
 #pragma unroll
@@ -1046,7 +1161,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
         const bool in = v < V && t < T1;
         const int vc = min(v, V - 1);
         x[e] = to_f32(lrow[vc]);
-        f[e] = __builtin_fmaf(alb, s[e], no_long ? 0.f : a.wl * x[e]);
+        f[e] = __builtin_fmaf(alb, s[e], a.wl * x[e]);
         if (a.prior) f[e] = minus_weighted(f[e], beb, a.prior[vc]);
         if (SAMPLE) f[e] *= a.smp.inv_temp;
         x[e] = in ? x[e] : -INFINITY;
@@ -1054,6 +1169,31 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
         f[e] = in ? f[e] : -INFINITY;
       }
     }
+    const float mx = max4(x), ms = max4(s), mf = max4(f);
+    if (__builtin_amdgcn_ballot_w64(fmaxf(fmaxf(mx - P.L.m, ms - P.S.m), mf - P.F.m) > kLag)) {
+      move_ref(P.L, nl, mx);
+      move_ref(P.S, ns, ms);
+      move_ref(P.F, nf, mf);
+    }
+  };
+  auto step = [&](int u, int i) {
+    const int t = T0 + (rev ? steps - 1 - i : i) * NSTR + str;
+    u32x4_t* buf = s_w + (PL::kBufs == 1 ? 0 : (i & 1) * NSTR * kTile);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      if (PACKED) {
+        buf[(MT == 1 ? str * kTile : 0) + piece(q)] = w[u][q];
+        continue;
+      }
+      const uint32_t row = __umul24(piece(q), recip) >> 18;
+      const int pc = piece(q) - (int)row * pr;
+      if (row < 16 * (MT == 1 ? 1 : NSTR))
+        buf[((MT == 1 ? str : 0) + (row >> 4)) * kTile + 16 * pc + ((row ^ pc) & 15)] = w[u][q];
+    }
+    const typename Four<LT>::type lcur = lg[u];
+    load_step(u, i + PD);
+    if (MT > 1) __syncthreads();
+    tile(t, buf + str * kTile, lcur);
   };
   for (int i = 0; i < steps; i += PD) {
 #pragma unroll
@@ -1118,13 +1258,13 @@ hipError_t launch_vocab_any(const VocabArgs<WT, LT>& a, const FinishArgs& fin, i
   return hipGetLastError();
 }
 
-template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE>
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED = false>
 hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
-  auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE>;
+  auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>;
   // the final merge takes 128 partials
   const size_t lds = std::max({VocabPlan<MT, KC, SAMPLE>::kLds + (a.prior ? kPriorTiles * 64 : 0), VocabPlan<MT, KC, SAMPLE>::act(SPL),
                                128 * sizeof(Partial)});
-  hipError_t e = raise_lds_limit<k_vocab<WT, LT, MT, KC, SPL, SAMPLE>>(lds);
+  hipError_t e = raise_lds_limit<k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>>(lds);
   if (e != hipSuccess) return e;
   kern<<<grid, kST, lds, st>>>(a, fin);
   return hipGetLastError();
@@ -1135,10 +1275,20 @@ hipError_t launch_vocab(const VocabArgs<WT, LT>& a, const FinishArgs& fin, hipSt
   constexpr int K1 = 128 / Op<WT>::KCH, K2 = 256 / Op<WT>::KCH;   // chunks of 128 and of 256 columns
   const unsigned gx = (unsigned)a.G;
   const int mt = (a.batch + 15) / 16;
-  if (a.r > 256 || a.long_only) {
+  // k_vocab_any also takes the rows without short logits, the fusion without long logits (whose
+  // masks are absent then) and a prior whose slice of a workgroup exceeds its room in LDS
+  const bool wide_prior = a.prior && (a.V + 15) / 16 / a.G + 1 + kSW > kPriorTiles;
+  if (a.r > 256 || a.long_only || a.wl == 0.f || wide_prior) {
     const int nkb = (a.r + 8 * Op<WT>::KCH - 1) / (8 * Op<WT>::KCH);
     return mt == 1 ? launch_vocab_any<WT, LT, 1, SPL, SAMPLE>(a, fin, nkb, dim3(gx, 1), st)
                    : launch_vocab_any<WT, LT, 2, SPL, SAMPLE>(a, fin, nkb, dim3(gx, (unsigned)((mt + 1) / 2)), st);
+  }
+  if constexpr (sizeof(WT) == 2) {
+    if (a.wv) {   // prepared heads come with r = 128 or 256 and more than 32 sequences
+      const dim3 grid(gx, (unsigned)((mt + 3) / 4));
+      return a.r <= 128 ? launch_vocab_k<WT, LT, 4, K1, SPL, SAMPLE, true>(a, fin, grid, st)
+                        : launch_vocab_k<WT, LT, 4, K2, SPL, SAMPLE, true>(a, fin, grid, st);
+    }
   }
   // as many tiles of 16 sequences per workgroup as the call has, at most four: the weights are
   // read once per workgroup row
@@ -1187,8 +1337,13 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     f.out_stats = a.out_stats;
     f.smp = a.smp;
     f.unc = a.unc;
+    f.hdr = a.hdr;
     return f;
   };
+  if (a.prep) {
+    k_check_prepared<<<1, 1, 0, st>>>(a.prep, *a.expect, a.hdr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   bool first_head_step = true;
   for (int j = 0; j < B; ++j) {
     const bool long_only = literal && j == 0;
@@ -1198,22 +1353,36 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     ts.G = G;
     const FinishArgs fin = finish_of(j ? j - 1 : 0);
     if (!long_only && !markov) {
-      GatesArgs<WT> ga;
-      ga.emb = (const WT*)hd.emb;
-      ga.w_ih = (const WT*)hd.w_ih;
-      ga.w_hh = (const WT*)hd.w_hh;
-      ga.d = hd.d;
-      ga.H = H;
-      ga.V = V;
-      ga.batch = batch;
-      ga.ts = ts;
-      ga.h_in = hc;
-      ga.h_zero = first_head_step;
-      ga.h_out = hn;
-      const unsigned gx = (unsigned)((H + kUnits - 1) / kUnits);
-      if (batch <= 16) k_gates<WT, 1><<<dim3(gx, 1), kST, 0, st>>>(ga);
-      else if (batch <= 32) k_gates<WT, 2><<<dim3(gx, 1), kST, 0, st>>>(ga);
-      else k_gates<WT, 4><<<dim3(gx, (unsigned)((batch + 63) / 64)), kST, 0, st>>>(ga);
+      if (a.T) {
+        FoldedArgs fa;
+        fa.T = a.T;
+        fa.whh = a.whh;
+        fa.H = H;
+        fa.V = V;
+        fa.batch = batch;
+        fa.ts = ts;
+        fa.h_in = hc;
+        fa.h_zero = first_head_step;
+        fa.h_out = hn;
+        k_gates_folded<<<dim3((unsigned)(H / 16), (unsigned)((batch + 15) / 16)), kST, 0, st>>>(fa);
+      } else {
+        GatesArgs<WT> ga;
+        ga.emb = (const WT*)hd.emb;
+        ga.w_ih = (const WT*)hd.w_ih;
+        ga.w_hh = (const WT*)hd.w_hh;
+        ga.d = hd.d;
+        ga.H = H;
+        ga.V = V;
+        ga.batch = batch;
+        ga.ts = ts;
+        ga.h_in = hc;
+        ga.h_zero = first_head_step;
+        ga.h_out = hn;
+        const unsigned gx = (unsigned)((H + kUnits - 1) / kUnits);
+        if (batch <= 16) k_gates<WT, 1><<<dim3(gx, 1), kST, 0, st>>>(ga);
+        else if (batch <= 32) k_gates<WT, 2><<<dim3(gx, 1), kST, 0, st>>>(ga);
+        else k_gates<WT, 4><<<dim3(gx, (unsigned)((batch + 63) / 64)), kST, 0, st>>>(ga);
+      }
       if ((e = hipGetLastError()) != hipSuccess) return e;
       RankArgs<WT> ra;
       ra.w_rank = (const WT*)hd.w_rank;
@@ -1230,6 +1399,7 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     }
     VocabArgs<WT, LT> va;
     va.w_vocab = (const WT*)hd.w_vocab;
+    va.wv = a.wv;
     va.V = V;
     va.r = r;
     va.batch = batch;

@@ -37,6 +37,7 @@ CASES = [
     (20011, 0, 0, 256, 4, 24, "bf16", "bf16", 0.0, True, False, True),
     (9973, 0, 0, 120, 5, 9, "f32", "f32", 0.7, False, True, True),
     (8200, 0, 0, 264, 4, 50, "bf16", "bf16", 0.0, True, False, True),
+    (520_001, 8, 8, 8, 2, 3, "bf16", "bf16", 0.0, True, False, False),   # the prior's slice exceeds its LDS
 ]
 
 
@@ -101,3 +102,36 @@ def test_unprepared_masks_and_ties(V, r, batch):
     lt.copy_(torch.from_numpy(long_h))
     _, st = run(0.5)
     assert torch.isnan(st[0, 2, 3]) and torch.isnan(st[0, 2, 5]) and torch.isfinite(st[0, :2, 3]).all()
+
+
+@pytest.mark.parametrize("V,r,batch,T,markov,literal", [
+    (5003, 128, 33, 0.0, False, True), (4099, 256, 65, 0.7, False, False), (5003, 128, 130, 0.0, False, False),
+    (7001, 256, 40, 0.7, True, True), (4100, 128, 64, 0.0, True, False)])
+def test_prepared_heads_of_many_sequences(V, r, batch, T, markov, literal):
+    """Above 32 sequences a prepared head is drafted by launches per position: against the oracle, with the
+    prior and per-position weights, the second call on the workspace bit for bit like the first."""
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=V, d=64, H=128, r=r, B=3, batch=batch, dtype="bf16", seed=40 + batch)
+    if markov:
+        em, wm = W.make_markov_head(V, r, "bf16", 40 + batch, scale=math.sqrt(3.0 / math.sqrt(r)))
+        head = B.LocalHead.markov_from_weights(em, wm)
+        oracle = O.MarkovHead(np.asarray(em, np.float64), np.asarray(wm, np.float64))
+    else:
+        hw = W.make_head(wl, "stress")
+        head, oracle = B.LocalHead.from_weights(hw), O.RnnHead.from_weights(hw)
+    head.prepare()
+    long_h, last, prior = W.make_long_logits(wl), W.make_last_token(wl), W.make_zipf_log_prior(V, 3)
+    al, be = [0.5, 0.55, 0.6], [0.3, 0.32, 0.34]
+    lt = B.as_tensor(long_h)
+    assert head.path(batch, 3, lt.dtype, True) == 1
+    ws = B.draft_workspace(head, batch, 3)
+    args = (head, lt, torch.from_numpy(np.asarray(last, np.int32)).cuda(),
+            torch.from_numpy(np.ascontiguousarray(prior, np.float32)).cuda(), 1.0, al, be)
+    kw = dict(first_row_long_only=literal, workspace=ws, temperature=T, seed=5)
+    tok, st = (x.clone() for x in B.draft_block(*args, **kw))
+    again = B.draft_block(*args, **kw)
+    torch.cuda.synchronize()
+    assert B.workspace_error(ws) == 0
+    assert torch.equal(tok, again[0]) and torch.equal(st.view(torch.int32), again[1].view(torch.int32))
+    rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, prior, 1.0, al, be, literal,
+                      temperature=T, seed=5)
+    assert all(e < 2e-4 for e in rep["errs"].values()), rep["errs"]
