@@ -110,7 +110,7 @@ def test_unprepared_masks_and_ties(V, r, batch):
 def test_prepared_heads_of_many_sequences(V, r, batch, T, markov, literal):
     """Above 32 sequences a prepared head is drafted by launches per position: against the oracle, with the
     prior and per-position weights, the second call on the workspace bit for bit like the first."""
-    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=V, d=64, H=128, r=r, B=3, batch=batch, dtype="bf16", seed=40 + batch)
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=V, d=64, H=256, r=r, B=3, batch=batch, dtype="bf16", seed=40 + batch)
     if markov:
         em, wm = W.make_markov_head(V, r, "bf16", 40 + batch, scale=math.sqrt(3.0 / math.sqrt(r)))
         head = B.LocalHead.markov_from_weights(em, wm)
