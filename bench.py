@@ -7,7 +7,7 @@ default workload is the largest single-GPU drafting configuration: batch 64, blo
 V = 151,936, embedding width 5120, GRU hidden 1024, rank 256, bf16 (Zipf-biased long logits).
 Inputs are seeded synthetic tensors already resident in HBM.  Prints one JSON line: the
 drafted-token throughput of the step, the roofline of the block's launches (the persistent drafting
-kernel up to 32 sequences) with warm and cold per-call timing distributions, and beside them the other launch mode,
+kernel up to 16 sequences) with warm and cold per-call timing distributions, and beside them the other launch mode,
 the block without statistics, the per-position launches, sampling at T = 1, adaptive fusion and
 its pre-pass, the Markov head, prior estimation, the standalone fused combine at the two serving
 shapes and every drafting workload; then the CPU oracle timed on the host in fresh subprocesses
@@ -302,7 +302,7 @@ def time_workload(B, W, wl, dev, torch, n=100):
     alg, _ = algorithmic_bytes(wl, 2 if wl.dtype == "bf16" else 4)
     comp = compulsory_bytes(wl, 2 if wl.dtype == "bf16" else 4)
     return {"batch": wl.batch, "B": wl.B, "V": V, "d": d, "H": H, "r": r, "dtype": wl.dtype,
-            "path": ("persistent" if wl.batch <= 32 else "prepared, per-position launches") if path == 1
+            "path": ("persistent" if wl.batch <= 16 else "prepared, per-position launches") if path == 1
                     else "per-position launches", "us_per_block": dist(us),
             "tokens_per_s": round(wl.batch * wl.B / (med * 1e-6), 1), "us_per_position": round(med / wl.B, 2),
             "algorithmic_bytes_per_block": alg, "roofline_frac": round(alg / (med * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
@@ -363,7 +363,7 @@ def main():
     torch.cuda.synchronize()
     L = B.as_tensor(long_h, dev)
     path = head.path(wl.batch, wl.B, L.dtype, False)
-    log(f"draft path: {('persistent' if wl.batch <= 32 else 'prepared, per-position launches') if path == 1 else 'per-position launches'}")
+    log(f"draft path: {('persistent' if wl.batch <= 16 else 'prepared, per-position launches') if path == 1 else 'per-position launches'}")
     last_t = torch.from_numpy(last).to(dev)
     tok = torch.empty((wl.batch, wl.B), dtype=torch.int32, device=dev)
     st = torch.empty((wl.batch, wl.B, 6), dtype=torch.float32, device=dev)
@@ -438,7 +438,7 @@ def main():
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic["traffic_bytes_per_launch"] if traffic else None,
-                "kernel": "k_draft_persistent (one launch per block)" if path == 1 and wl.batch <= 32 else
+                "kernel": "k_draft_persistent (one launch per block)" if path == 1 and wl.batch <= 16 else
                           "dls_draft_block (all launches of one block)",
                 "us_per_launch": round(blk_us, 2),
                 "algorithmic_bytes_per_launch": alg_block,

@@ -426,7 +426,7 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
   a.unc = out_unc;
   if (head->prepared) {
     // The prepared form is used where the persistent kernel's plan holds for the call, kMaxBatch
-    // sequences at a time: by that kernel up to kPersistBatch sequences, by the launches per
+    // sequences at a time: by that kernel up to persist_batch sequences, by the launches per
     // position above.
     const int nfull = std::min<int32_t>(batch, dls::kMaxBatch);
     const int nlast = batch - (batch - 1) / dls::kMaxBatch * dls::kMaxBatch;   // the last launch's sequences
@@ -448,7 +448,7 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
       expect.w_ih = ch.w_ih;
       expect.w_hh = ch.w_hh;
       expect.w_vocab = ch.w_vocab;
-      if (batch > dls::kPersistBatch) {
+      if (batch > dls::persist_batch(ch.kind == DLS_HEAD_MARKOV)) {
         a.T = ch.kind == DLS_HEAD_MARKOV ? nullptr : (const float*)(pp + PL.off_T);
         a.wv = (const uint4*)(pp + PL.off_wv);
         a.whh = (const uint4*)(pp + PL.off_whh);

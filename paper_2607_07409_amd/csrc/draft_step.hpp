@@ -1284,7 +1284,10 @@ hipError_t launch_vocab(const VocabArgs<WT, LT>& a, const FinishArgs& fin, hipSt
                    : launch_vocab_any<WT, LT, 2, SPL, SAMPLE>(a, fin, nkb, dim3(gx, (unsigned)((mt + 1) / 2)), st);
   }
   if constexpr (sizeof(WT) == 2) {
-    if (a.wv) {   // prepared heads come with r = 128 or 256 and more than 32 sequences
+    if (a.wv) {   // prepared heads come with r = 128 or 256 and more than 16 sequences
+      if (mt == 2)
+        return a.r <= 128 ? launch_vocab_k<WT, LT, 2, K1, SPL, SAMPLE, true>(a, fin, dim3(gx, 1), st)
+                          : launch_vocab_k<WT, LT, 2, K2, SPL, SAMPLE, true>(a, fin, dim3(gx, 1), st);
       const dim3 grid(gx, (unsigned)((mt + 3) / 4));
       return a.r <= 128 ? launch_vocab_k<WT, LT, 4, K1, SPL, SAMPLE, true>(a, fin, grid, st)
                         : launch_vocab_k<WT, LT, 4, K2, SPL, SAMPLE, true>(a, fin, grid, st);

@@ -106,9 +106,10 @@ def test_unprepared_masks_and_ties(V, r, batch):
 
 @pytest.mark.parametrize("V,r,batch,T,markov,literal", [
     (5003, 128, 33, 0.0, False, True), (4099, 256, 65, 0.7, False, False), (5003, 128, 130, 0.0, False, False),
-    (7001, 256, 40, 0.7, True, True), (4100, 128, 64, 0.0, True, False)])
+    (7001, 256, 40, 0.7, True, True), (4100, 128, 64, 0.0, True, False), (5003, 128, 17, 0.7, False, True),
+    (7001, 256, 32, 0.0, False, False), (4099, 256, 17, 0.0, False, True), (5003, 128, 31, 0.7, False, False)])
 def test_prepared_heads_of_many_sequences(V, r, batch, T, markov, literal):
-    """Above 32 sequences a prepared head is drafted by launches per position: against the oracle, with the
+    """Above 16 sequences (a Markov head: 32) a prepared head is drafted by launches per position: against the oracle, with the
     prior and per-position weights, the second call on the workspace bit for bit like the first."""
     wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=V, d=64, H=256, r=r, B=3, batch=batch, dtype="bf16", seed=40 + batch)
     if markov:
