@@ -270,9 +270,35 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int b, Partial* 
     f.out_tokens[(size_t)b * f.B + f.j] = t;
   }
 }
-__global__ __launch_bounds__(kST) void k_finish(FinishArgs f) {
+// The block's last launch also clears what its launches wrote into the workspace (float32 state, keys and
+// partials): the persistent kernel takes a word of a workspace for its own by the tag in its upper
+// half, and its words of another batch or block length lie where these lay.  About 18 KB a sequence.
+struct ClearArgs {
+  float *h0, *h1, *rho;   // [batch][H], [batch][H], [batch][r]; NULL: a head without them
+  int H, r;
+  uint64_t* keys;         // [sets][batch][G]
+  StepPart* parts;
+  int sets;
+};
+__global__ __launch_bounds__(kST) void k_finish(FinishArgs f, ClearArgs c) {
   __shared__ Partial sh[kSW];
-  finish_row(f, blockIdx.x, sh);
+  const size_t b = blockIdx.x;
+  finish_row(f, (int)b, sh);
+  __syncthreads();
+  const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (c.h0) {
+    for (int i = threadIdx.x; i < c.H / 4; i += kST) {
+      reinterpret_cast<float4*>(c.h0 + b * c.H)[i] = z;
+      reinterpret_cast<float4*>(c.h1 + b * c.H)[i] = z;
+    }
+    for (int i = threadIdx.x; i < c.r / 4; i += kST) reinterpret_cast<float4*>(c.rho + b * c.r)[i] = z;
+  }
+  for (int s = 0; s < c.sets; ++s) {
+    const size_t o = ((size_t)s * f.batch + b) * f.G;
+    uint32_t* p = reinterpret_cast<uint32_t*>(c.parts + o);
+    for (int i = threadIdx.x; i < f.G; i += kST) c.keys[o + i] = 0ull;
+    for (int i = threadIdx.x; i < f.G * (int)(sizeof(StepPart) / 4); i += kST) p[i] = 0u;
+  }
 }
 
 // ----------------------------------------------------------------------------------
@@ -1428,7 +1454,16 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     e = markov ? launch_vocab<WT, LT, 1, SAMPLE>(va, fin, st) : launch_vocab<WT, LT, Op<WT>::SPL, SAMPLE>(va, fin, st);
     if (e != hipSuccess) return e;
   }
-  k_finish<<<batch, kST, 0, st>>>(finish_of(B - 1));
+  ClearArgs ca;
+  ca.h0 = markov ? nullptr : hc;
+  ca.h1 = hn;
+  ca.rho = rho;
+  ca.H = H;
+  ca.r = r;
+  ca.keys = keys;
+  ca.parts = parts;
+  ca.sets = markov ? 2 : 1;
+  k_finish<<<batch, kST, 0, st>>>(finish_of(B - 1), ca);
   return hipGetLastError();
 }
 

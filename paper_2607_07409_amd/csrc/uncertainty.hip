@@ -171,13 +171,16 @@ __global__ __launch_bounds__(kThreads) void k_unc_part(const T* __restrict__ L, 
   }
 }
 
-// one wave per row: lane i merges ranges i, i + 64, ... in order, then the wave merges the lanes
-__global__ __launch_bounds__(64) void k_unc_merge(const float4* __restrict__ parts_in, int parts, UncRule ru,
+// one wave per row: lane i merges ranges i, i + 64, ... in order, then the wave merges the lanes.  The
+// partials are cleared on the way: in a drafting workspace only words with a tag of the persistent
+// kernel or zeros may stay behind.
+__global__ __launch_bounds__(64) void k_unc_merge(float4* __restrict__ parts_in, int parts, UncRule ru,
                                                   dls_row_uncertainty* __restrict__ out) {
   const int row = blockIdx.x, lane = threadIdx.x;
   Ent a = ent_empty();
   for (int i = lane; i < parts; i += 64) {
     const float4 p = parts_in[(size_t)row * parts + i];
+    parts_in[(size_t)row * parts + i] = make_float4(0.f, 0.f, 0.f, 0.f);
     a = ent_merge(a, Ent{p.x, p.y, p.z});
   }
   a = ent_wave_merge(a);

@@ -75,6 +75,36 @@ def test_prepared_buffer_of_another_head_is_refused(i):
     assert B.workspace_error(ws2) == 0 and B.workspace_error(ws) == 0
 
 
+@pytest.mark.parametrize("markov,prepared,batch,adaptive", [
+    (False, True, 17, False), (True, True, 33, False), (False, True, 20, True), (False, False, 17, False),
+    (True, False, 3, True), (False, True, 3, True)])
+def test_calls_leave_only_tagged_words(markov, prepared, batch, adaptive):
+    """Calls of several shapes and routes share a workspace, whose regions move with the shape, and the
+    persistent kernel trusts any word that carries its tag.  So float32 state, keys and partials may not stay
+    behind: the launches per position leave the workspace as they found it, and the uncertainty pass its region
+    (the last one)."""
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=20_011, d=64, H=128, r=128, B=5, batch=batch, dtype="bf16")
+    if markov:
+        head = B.LocalHead.markov_from_weights(*W.make_markov_head(wl.V, wl.r, "bf16", 3, scale=0.5))
+    else:
+        head = B.LocalHead.from_weights(W.make_head(wl, "stress"))
+    if prepared:
+        head.prepare()
+    lt = B.as_tensor(W.make_long_logits(wl))
+    last = torch.from_numpy(W.make_last_token(wl)).cuda()
+    ws = B.draft_workspace(head, wl.batch, wl.B)
+    B.draft_block(head, lt, last, None, 1.0, 0.5, 0.0, workspace=ws,
+                  adaptive=(B.UNC_ENTROPY, 0.1, 0.7) if adaptive else None)
+    torch.cuda.synchronize()
+    rows = wl.batch * wl.B
+    tail = (B.lib().dls_long_uncertainty_workspace_size(rows, wl.V) + 255) // 256 * 256
+    assert tail > 0
+    persistent = int(ws[0:4].view(torch.int32).item()) > 0   # the call epoch
+    assert persistent == (prepared and batch == 3)
+    left = ws[ws.numel() - tail:] if persistent else ws
+    assert int(left.count_nonzero().item()) == 0
+
+
 def test_error_query_is_stream_ordered():
     """dls_draft_block_error reads the word after the work queued before it on the stream."""
     wl, head, lt, last = _setup(0)
