@@ -136,3 +136,25 @@ def test_prepared_heads_of_many_sequences(V, r, batch, T, markov, literal):
     rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, prior, 1.0, al, be, literal,
                       temperature=T, seed=5)
     assert all(e < 2e-4 for e in rep["errs"].values()), rep["errs"]
+
+
+@pytest.mark.parametrize("prepared,batch", [(False, 40), (True, 17), (True, 40)])
+def test_log_sum_exp_precision(prepared, batch):
+    """Rows of log-probabilities with one confident token: their log-sum-exp is 0, and what a kernel loses shows
+    whole.  The token's own term is exactly 1 where the reference is the maximum; about thirty additions to a
+    sum between 1 and 2 round by 2^-23 / sqrt(12) each, 1.9e-7 together (root mean square); a reference that lies
+    30 below rounds the exponent itself by up to 2^-19."""
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=20_011, d=64, H=128, r=128, B=16, batch=batch, dtype="bf16", seed=3)
+    head = B.LocalHead.from_weights(W.make_head(wl, "stress"))
+    if prepared:
+        head.prepare()
+    g = torch.Generator().manual_seed(batch)
+    x = 3.0 * torch.randn(batch * wl.B, wl.V, generator=g, dtype=torch.float64)
+    x.scatter_add_(1, torch.randint(0, wl.V, (batch * wl.B, 1), generator=g), torch.full((batch * wl.B, 1), 24.0, dtype=torch.float64))
+    long = torch.log_softmax(x, -1).float()
+    want = long.double().logsumexp(-1)
+    _, st = B.draft_block(head, long.cuda().view(batch, wl.B, wl.V), torch.from_numpy(W.make_last_token(wl)).cuda(), None,
+                          1.0, 0.5, 0.0)
+    err = (st.cpu().view(-1, 6)[:, B.STATS_FIELDS.index("lse_long")].double() - want).abs()
+    print(prepared, batch, err.mean().item(), err.max().item())
+    assert err.mean() < 3e-7
