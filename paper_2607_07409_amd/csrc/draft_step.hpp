@@ -28,6 +28,19 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4_t;   // arrays of it stay in registers
+// LDS is read and written through pointers of its own address space: through a generic pointer the
+// compiler may merge an access with one of global memory into a FLAT access.
+typedef __attribute__((address_space(3))) u32x4_t lds_u32x4;
+typedef __attribute__((address_space(3))) f32x4_t lds_f32x4;
+typedef __attribute__((address_space(3))) float lds_float;
+__device__ __forceinline__ u32x4_t vec(uint4 v) { return u32x4_t{v.x, v.y, v.z, v.w}; }
+__device__ __forceinline__ uint4 unvec(u32x4_t v) { return make_uint4(v.x, v.y, v.z, v.w); }
+// LDS of a wave alone: accesses before are ordered before those after, for all its lanes
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
 
 constexpr int kST = 512;             // threads per workgroup
 constexpr int kSW = kST / 64;
@@ -694,13 +707,13 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
   // activations of the 16 MT sequences as operands in LDS: [m][chunk][split][lane] of 16 bytes.
   // Loads return in order: the activations are asked for before the weights, which then arrive
   // while the operands are staged.
-  uint4* s_b = reinterpret_cast<uint4*>(smem);
+  lds_u32x4* s_b = (lds_u32x4*)smem;
   const int kc = nkb * KCB;
   auto put = [&](int i, const uint4* o) {
     const int s = i / (kc * 4), pc = i % (kc * 4);
 #pragma unroll
     for (int e = 0; e < SPL; ++e)
-      s_b[(((size_t)(s >> 4) * kc + (pc >> 2)) * SPL + e) * 64 + 16 * (pc & 3) + (s & 15)] = o[e];
+      s_b[(((s >> 4) * kc + (pc >> 2)) * SPL + e) * 64 + 16 * (pc & 3) + (s & 15)] = vec(o[e]);
   };
   auto piece_ok = [&](int i) { return (i % (kc * 4)) * O::NP < r && b0 + i / (kc * 4) < a.batch; };
   auto piece_col = [&](int i) { return (i % (kc * 4)) * O::NP < r ? (i % (kc * 4)) * O::NP : 0; };
@@ -795,12 +808,12 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
         }
 #pragma unroll
         for (int m = 0; m < MT; ++m) {
-          const uint4* sb = s_b + ((size_t)m * kc + kb * KCB) * SPL * 64 + lane;
+          const lds_u32x4* sb = s_b + (m * kc + kb * KCB) * SPL * 64 + lane;
 #pragma unroll
           for (int c = 0; c < KCB; ++c)
 #pragma unroll
             for (int e = SPL - 1; e >= 0; --e) {
-              const uint4 bb = sb[(c * SPL + e) * 64];
+              const uint4 bb = unvec(sb[(c * SPL + e) * 64]);
               acc[m][0] = O::mma(t.A[0][c], bb, acc[m][0]);
               acc[m][1] = O::mma(t.A[1][c], bb, acc[m][1]);
             }
@@ -973,7 +986,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   const int mt = wave % MT, str = wave / MT;
   const int b = b0 + 16 * mt + n, bc = min(b, a.batch - 1);
   const LT* lrow = a.L + (size_t)bc * a.bstride;
-  u32x4_t* s_w = reinterpret_cast<u32x4_t*>(smem);
+  lds_u32x4* s_w = (lds_u32x4*)smem;
   const bool rev = (a.j & 1) != 0;
 
   // Pieces of a step are dealt out in memory order: with MT = 1 a wave takes its own tile, else the
@@ -1004,20 +1017,20 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   // while the operands are made.
   // The workgroup's slice of the prior goes to LDS with them.
   constexpr int NA = (MT * KC * 64 + kST - 1) / kST;
-  float* s_prior = reinterpret_cast<float*>(smem + PL::kLds);
+  lds_float* s_prior = (lds_float*)(smem + PL::kLds);
   const bool staged = a.prior != nullptr;   // the slice fits: T1 - T0 + NSTR <= kPriorTiles
   float pv0[kPriorTiles * 16 / kST];
   if (staged) {
 #pragma unroll
     for (int q = 0; q < kPriorTiles * 16 / kST; ++q) pv0[q] = a.prior[min(16 * T0 + tid + q * kST, V - 1)];
   }
-  uint4* s_a = reinterpret_cast<uint4*>(smem);
+  lds_u32x4* s_a = (lds_u32x4*)smem;
   uint4 act[KC][SPL];
   {
     auto put = [&](int i, const uint4* o) {   // piece i: sequence i / (4 KC), piece i % (4 KC) of its row
       const int s = i / (4 * KC), pc = i % (4 * KC);
 #pragma unroll
-      for (int e = 0; e < SPL; ++e) s_a[(((s >> 4) * KC + (pc >> 2)) * SPL + e) * 64 + 16 * (pc & 3) + (s & 15)] = o[e];
+      for (int e = 0; e < SPL; ++e) s_a[(((s >> 4) * KC + (pc >> 2)) * SPL + e) * 64 + 16 * (pc & 3) + (s & 15)] = vec(o[e]);
     };
     if (a.e_m) {
       TokenKeys<2 * MT> tk;
@@ -1066,7 +1079,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
 #pragma unroll
     for (int c = 0; c < KC; ++c)
 #pragma unroll
-      for (int e = 0; e < SPL; ++e) act[c][e] = s_a[((mt * KC + c) * SPL + e) * 64 + lane];
+      for (int e = 0; e < SPL; ++e) act[c][e] = unvec(s_a[((mt * KC + c) * SPL + e) * 64 + lane]);
     __syncthreads();
     if (staged) {
 #pragma unroll
@@ -1136,13 +1149,12 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
     P.i1 = up ? mi : P.i1;
     P.t1 = up ? m1 : P.t1;
   };
-  auto tile = [&](int t, const u32x4_t* sb, typename Four<LT>::type lcur) {
+  auto tile = [&](int t, const lds_u32x4* sb, typename Four<LT>::type lcur) {
     uint4 A[KC];
 #pragma unroll
     for (int c = 0; c < KC; ++c) {
       const int pc = 4 * c + g;
-      const u32x4_t raw = sb[PACKED ? c * 64 + lane : 16 * pc + (n ^ (pc & 15))];
-      A[c] = make_uint4(raw.x, raw.y, raw.z, raw.w);
+      A[c] = unvec(sb[PACKED ? c * 64 + lane : 16 * pc + (n ^ (pc & 15))]);
     }
     f32x4_t acc[SPL];
 #pragma unroll
@@ -1152,9 +1164,8 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
 #pragma unroll
       for (int e = SPL - 1; e >= 0; --e) acc[e] = O::mma(A[c], act[c][e], acc[e]);
     fold();
-    // Four sequence tiles: products and fold share the wave's issue slots (33.3 -> 30.2 us together with
-    // lagging references).  With fewer the stream of weights is the bound, and the registers
-    // that the interleaving takes would spill.
+    // Four sequence tiles: products and fold share the wave's issue slots.  With fewer the stream of
+    // weights is the bound, and the registers that the interleaving takes would spill.
     constexpr int kMfma = KC * (sizeof(WT) == 2 ? SPL : 4);
     constexpr int kValu = ((SAMPLE ? 300 : 100) + kMfma - 1) / kMfma;
 #pragma unroll
@@ -1170,7 +1181,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
       f[e] = __builtin_fmaf(alb, s[e], a.wl * x[e]);
     }
     if (a.prior) {   // uniform
-      const float4 pv = *reinterpret_cast<const float4*>(s_prior + vp - 16 * T0);
+      const f32x4_t pv = *(const lds_f32x4*)(s_prior + vp - 16 * T0);
       const float pe[4] = {pv.x, pv.y, pv.z, pv.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) f[e] = __builtin_fmaf(-beb, no_prior ? 0.f : pe[e], f[e]);
@@ -1200,7 +1211,8 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   };
   auto step = [&](int u, int i) {
     const int t = T0 + (rev ? steps - 1 - i : i) * NSTR + str;
-    u32x4_t* buf = s_w + (PL::kBufs == 1 ? 0 : (i & 1) * NSTR * kTile);
+    if (MT == 1) wave_lds_order();   // the operands of the step before are read
+    lds_u32x4* buf = s_w + (PL::kBufs == 1 ? 0 : (i & 1) * NSTR * kTile);
 #pragma unroll
     for (int q = 0; q < NP; ++q) {
       if (PACKED) {
@@ -1215,6 +1227,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
     const typename Four<LT>::type lcur = lg[u];
     load_step(u, i + PD);
     if (MT > 1) __syncthreads();
+    else wave_lds_order();
     tile(t, buf + str * kTile, lcur);
   };
   for (int i = 0; i < steps; i += PD) {

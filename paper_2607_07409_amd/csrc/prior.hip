@@ -110,13 +110,15 @@ __global__ __launch_bounds__(kCT) void k_count_sliced(const int32_t* __restrict_
 constexpr int kSlotBits = 14;
 constexpr int kSlots = 1 << kSlotBits;  // 128 KiB of LDS
 
+// an LDS read (through a generic pointer a volatile read is a FLAT access)
+typedef volatile __attribute__((address_space(3))) unsigned long long lds_slot;
 __device__ __forceinline__ void count_token(unsigned long long* tab, int t, uint64_t* __restrict__ counts) {
   const uint64_t key = (uint64_t)(uint32_t)(t + 1) << 32;
   const uint32_t h = ((uint32_t)t * 2654435761u) >> (32 - kSlotBits);
 #pragma unroll
   for (int p = 0; p < 2; ++p) {
     unsigned long long* slot = tab + (h ^ (uint32_t)p);
-    unsigned long long cur = *(volatile unsigned long long*)slot;
+    unsigned long long cur = *(lds_slot*)slot;
     if (cur == 0ull) cur = atomicCAS(slot, 0ull, (unsigned long long)(key | 1ull));
     if (cur == 0ull) return;                                   // claimed with a count of one
     if ((cur & 0xffffffff00000000ull) == key) {                // the token's own slot
