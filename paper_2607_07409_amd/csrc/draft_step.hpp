@@ -956,12 +956,15 @@ template <> struct Four<float> {
   }
 };
 constexpr int kPriorTiles = 128;   // tiles of prior entries a workgroup keeps in LDS (8 KB)
-template <int MT, int KC, bool SAMPLE>
+template <int MT, int KC>
 struct VocabPlan {
   static constexpr int NSTR = kSW / MT;                           // tiles per step
   static constexpr int NP = NSTR * KC / kSW;                      // 16-byte pieces per thread and step
-  // as deep as the registers allow without spills (the noise of a sampled row takes some)
-  static constexpr int PD = NP >= 16 ? 1 : NP >= 8 ? (SAMPLE ? 1 : 2) : NP >= 4 ? 3 : NP >= 2 ? 6 : 8;
+  // Steps in flight, as deep as pays: none of these spills, and one or two steps more do (12 to 60
+  // registers) without being faster where they do not.  us a block at V = 151,936, H = 1,024, r = 256 in bf16, these
+  // and 2, 3, 6, 8: prepared batch 64 651 and 676, sampled 756 and 783, batch 32 515 and 529; unprepared
+  // batch 32 361 and 392, 1 263 and 269 (8 positions).  r = 128, H = 512, batch 64: 554 and 581.
+  static constexpr int PD = NP >= 8 ? 1 : NP >= 4 ? 2 : 4;
   static constexpr int kTile = KC * 64;                           // pieces of a tile in LDS
   static constexpr int kBufs = MT == 1 ? 1 : 2;                   // a wave alone needs no second buffer
   static constexpr size_t kLds = (size_t)kBufs * NSTR * kTile * 16;
@@ -972,7 +975,7 @@ struct VocabPlan {
 template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED>
 __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArgs fin) {
   using O = Op<WT>;
-  using PL = VocabPlan<MT, KC, SAMPLE>;
+  using PL = VocabPlan<MT, KC>;
   constexpr int NSTR = PL::NSTR, NP = PL::NP, PD = PL::PD, NF = O::NP / 4, kTile = PL::kTile;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ int s_tok[16 * MT];
@@ -1164,15 +1167,6 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
 #pragma unroll
       for (int e = SPL - 1; e >= 0; --e) acc[e] = O::mma(A[c], act[c][e], acc[e]);
     fold();
-    // Four sequence tiles: products and fold share the wave's issue slots.  With fewer the stream of
-    // weights is the bound, and the registers that the interleaving takes would spill.
-    constexpr int kMfma = KC * (sizeof(WT) == 2 ? SPL : 4);
-    constexpr int kValu = ((SAMPLE ? 300 : 100) + kMfma - 1) / kMfma;
-#pragma unroll
-    for (int q = 0; q < (MT == 4 ? kMfma : 0); ++q) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);         // a matrix instruction
-      __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);     // vector instructions of the fold
-    }
     vp = 16 * t + 4 * g;
     Four<LT>::widen(lcur, x);
 #pragma unroll
@@ -1297,7 +1291,7 @@ template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool P
 hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
   auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>;
   // the final merge takes 128 partials
-  const size_t lds = std::max({VocabPlan<MT, KC, SAMPLE>::kLds + (a.prior ? kPriorTiles * 64 : 0), VocabPlan<MT, KC, SAMPLE>::act(SPL),
+  const size_t lds = std::max({VocabPlan<MT, KC>::kLds + (a.prior ? kPriorTiles * 64 : 0), VocabPlan<MT, KC>::act(SPL),
                                128 * sizeof(Partial)});
   hipError_t e = raise_lds_limit<k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>>(lds);
   if (e != hipSuccess) return e;
