@@ -955,6 +955,12 @@ template <> struct Four<float> {
     x[3] = v.w;
   }
 };
+// weighted(w, x) in one instruction: w x, and 0 where w is 0, whatever x (-inf masks and NaN included)
+__device__ __forceinline__ float mul_weight(float w, float x) {
+  float r;
+  asm("v_mul_legacy_f32 %0, %1, %2" : "=v"(r) : "s"(w), "v"(x));
+  return r;
+}
 constexpr int kPriorTiles = 128;   // tiles of prior entries a workgroup keeps in LDS (8 KB)
 template <int MT, int KC>
 struct VocabPlan {
@@ -1172,7 +1178,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       s[e] = SPL == 3 ? (acc[SPL - 1][e] + acc[SPL / 2][e]) + acc[0][e] : acc[0][e];
-      f[e] = __builtin_fmaf(alb, s[e], a.wl * x[e]);
+      f[e] = __builtin_fmaf(alb, s[e], mul_weight(a.wl, x[e]));
     }
     if (a.prior) {   // uniform
       const f32x4_t pv = *(const lds_f32x4*)(s_prior + vp - 16 * T0);
@@ -1191,7 +1197,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
         const bool in = v < V && t < T1;
         const int vc = min(v, V - 1);
         x[e] = to_f32(lrow[vc]);
-        f[e] = __builtin_fmaf(alb, s[e], a.wl * x[e]);
+        f[e] = __builtin_fmaf(alb, s[e], mul_weight(a.wl, x[e]));
         if (a.prior) f[e] = minus_weighted(f[e], beb, a.prior[vc]);
         if (SAMPLE) f[e] *= a.smp.inv_temp;
         x[e] = in ? x[e] : -INFINITY;
@@ -1304,10 +1310,10 @@ hipError_t launch_vocab(const VocabArgs<WT, LT>& a, const FinishArgs& fin, hipSt
   constexpr int K1 = 128 / Op<WT>::KCH, K2 = 256 / Op<WT>::KCH;   // chunks of 128 and of 256 columns
   const unsigned gx = (unsigned)a.G;
   const int mt = (a.batch + 15) / 16;
-  // k_vocab_any also takes the rows without short logits, the fusion without long logits (whose
-  // masks are absent then) and a prior whose slice of a workgroup exceeds its room in LDS
+  // k_vocab_any also takes the rows without short logits and a prior whose slice of a workgroup exceeds
+  // its room in LDS
   const bool wide_prior = a.prior && (a.V + 15) / 16 / a.G + 1 + kSW > kPriorTiles;
-  if (a.r > 256 || a.long_only || a.wl == 0.f || wide_prior) {
+  if (a.r > 256 || a.long_only || wide_prior) {
     const int nkb = (a.r + 8 * Op<WT>::KCH - 1) / (8 * Op<WT>::KCH);
     return mt == 1 ? launch_vocab_any<WT, LT, 1, SPL, SAMPLE>(a, fin, nkb, dim3(gx, 1), st)
                    : launch_vocab_any<WT, LT, 2, SPL, SAMPLE>(a, fin, nkb, dim3(gx, (unsigned)((mt + 1) / 2)), st);

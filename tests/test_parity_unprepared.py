@@ -158,3 +158,22 @@ def test_log_sum_exp_precision(prepared, batch):
     err = (st.cpu().view(-1, 6)[:, B.STATS_FIELDS.index("lse_long")].double() - want).abs()
     print(prepared, batch, err.mean().item(), err.max().item())
     assert err.mean() < 3e-7
+
+
+@pytest.mark.parametrize("prepared,batch,T", [(False, 3, 0.7), (True, 20, 0.0), (True, 40, 0.7), (False, 20, 0.0)])
+def test_no_long_term(prepared, batch, T):
+    """w_long = 0 with masked long logits: the long term is absent, masks included, and the head and the prior
+    decide alone, at one, two and four tiles of sequences."""
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=20_011, d=64, H=256, r=128, B=3, batch=batch, dtype="bf16", seed=8)
+    hw = W.make_head(wl, "stress")
+    head, oracle = B.LocalHead.from_weights(hw), O.RnnHead.from_weights(hw)
+    if prepared:
+        head.prepare()
+    long_h = np.asarray(W.make_long_logits(wl), np.float32).copy()
+    long_h[:, :, ::3] = -np.inf
+    last, prior = W.make_last_token(wl), W.make_zipf_log_prior(wl.V, 3)
+    tok, st = B.draft_block(head, torch.from_numpy(long_h).cuda(), torch.from_numpy(np.asarray(last, np.int32)).cuda(),
+                            torch.from_numpy(np.ascontiguousarray(prior, np.float32)).cuda(), 0.0, 0.5, 0.3,
+                            temperature=T, seed=5)
+    rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, prior, 0.0, 0.5, 0.3, temperature=T, seed=5)
+    assert all(e < 2e-4 for e in rep["errs"].values()), rep["errs"]
