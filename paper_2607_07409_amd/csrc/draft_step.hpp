@@ -283,6 +283,11 @@ __device__ __forceinline__ void finish_row(const FinishArgs& f, int b, Partial* 
     f.out_tokens[(size_t)b * f.B + f.j] = t;
   }
 }
+// the row of a further workgroup of the vocabulary launch
+__device__ __forceinline__ void finish_extra(const FinishArgs& f, int G, Partial* sh) {
+  const int row = (int)((blockIdx.x - G) * gridDim.y + blockIdx.y);
+  if (row < f.batch) finish_row(f, row, sh);
+}
 // The block's last launch also clears what its launches wrote into the workspace (float32 state, keys and
 // partials): the persistent kernel takes a word of a workspace for its own by the tag in its upper
 // half, and its words of another batch or block length lie where these lay.  About 18 KB a sequence.
@@ -607,7 +612,8 @@ struct VocabArgs {
   const dls_row_uncertainty* unc;
   uint64_t* keys;
   StepPart* parts;
-  int finish;                    // the workgroups also write the results of the position before
+  int finish;                    // the results of the position before are written by: 0 nobody, 1 the workgroups,
+                                 // at their end, 2 further workgroups (blockIdx.x >= G)
 };
 
 struct __attribute__((packed, aligned(2))) Raw16 { uint32_t x, y, z, w; };
@@ -665,6 +671,10 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
   constexpr int NL = sizeof(LT) == 2 ? 1 : 2;   // 16-byte pieces of eight long logits
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ int s_tok[16 * MT];
+  if ((int)blockIdx.x >= a.G) {
+    finish_extra(fin, a.G, reinterpret_cast<Partial*>(smem));
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n = lane & 15, g = lane >> 4;
   const int b0 = blockIdx.y * 16 * MT;
@@ -905,9 +915,9 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
       a.parts[o] = StepPart{Q.L.m, Q.L.s, Q.S.m, Q.S.s, Q.F.m, Q.F.s, Q.t2};
     }
   }
-  if (a.finish && blockIdx.y == 0) {   // uniform
+  if (a.finish == 1 && blockIdx.y == 0) {   // uniform; G >= batch
     __syncthreads();
-    for (int row = blockIdx.x; row < a.batch; row += a.G) finish_row(fin, row, sp);
+    if ((int)blockIdx.x < a.batch) finish_row(fin, blockIdx.x, sp);
   }
 }
 
@@ -985,6 +995,10 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   constexpr int NSTR = PL::NSTR, NP = PL::NP, PD = PL::PD, NF = O::NP / 4, kTile = PL::kTile;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   __shared__ int s_tok[16 * MT];
+  if ((int)blockIdx.x >= a.G) {
+    finish_extra(fin, a.G, reinterpret_cast<Partial*>(smem));
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int b0 = blockIdx.y * 16 * MT;
@@ -1255,9 +1269,9 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
       a.parts[o] = StepPart{Q.L.m, Q.L.s, Q.S.m, Q.S.s, Q.F.m, Q.F.s, Q.t2};
     }
   }
-  if (a.finish && blockIdx.y == 0) {   // uniform
+  if (a.finish == 1 && blockIdx.y == 0) {   // uniform; G >= batch
     __syncthreads();
-    for (int row = blockIdx.x; row < a.batch; row += a.G) finish_row(fin, row, sp);
+    if ((int)blockIdx.x < a.batch) finish_row(fin, blockIdx.x, sp);
   }
 }
 
@@ -1293,7 +1307,7 @@ hipError_t launch_vocab_any(const VocabArgs<WT, LT>& a, const FinishArgs& fin, i
   return hipGetLastError();
 }
 
-template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED = false>
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED>
 hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
   auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>;
   // the final merge takes 128 partials
@@ -1306,34 +1320,43 @@ hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim
 }
 
 template <typename WT, typename LT, int SPL, bool SAMPLE>
-hipError_t launch_vocab(const VocabArgs<WT, LT>& a, const FinishArgs& fin, hipStream_t st) {
+hipError_t launch_vocab(VocabArgs<WT, LT> a, const FinishArgs& fin, hipStream_t st) {
   constexpr int K1 = 128 / Op<WT>::KCH, K2 = 256 / Op<WT>::KCH;   // chunks of 128 and of 256 columns
-  const unsigned gx = (unsigned)a.G;
   const int mt = (a.batch + 15) / 16;
   // k_vocab_any also takes the rows without short logits and a prior whose slice of a workgroup exceeds
   // its room in LDS
   const bool wide_prior = a.prior && (a.V + 15) / 16 / a.G + 1 + kSW > kPriorTiles;
-  if (a.r > 256 || a.long_only || wide_prior) {
-    const int nkb = (a.r + 8 * Op<WT>::KCH - 1) / (8 * Op<WT>::KCH);
-    return mt == 1 ? launch_vocab_any<WT, LT, 1, SPL, SAMPLE>(a, fin, nkb, dim3(gx, 1), st)
-                   : launch_vocab_any<WT, LT, 2, SPL, SAMPLE>(a, fin, nkb, dim3(gx, (unsigned)((mt + 1) / 2)), st);
-  }
-  if constexpr (sizeof(WT) == 2) {
-    if (a.wv) {   // prepared heads come with r = 128 or 256 and more than 16 sequences
-      if (mt == 2)
-        return a.r <= 128 ? launch_vocab_k<WT, LT, 2, K1, SPL, SAMPLE, true>(a, fin, dim3(gx, 1), st)
-                          : launch_vocab_k<WT, LT, 2, K2, SPL, SAMPLE, true>(a, fin, dim3(gx, 1), st);
-      const dim3 grid(gx, (unsigned)((mt + 3) / 4));
-      return a.r <= 128 ? launch_vocab_k<WT, LT, 4, K1, SPL, SAMPLE, true>(a, fin, grid, st)
-                        : launch_vocab_k<WT, LT, 4, K2, SPL, SAMPLE, true>(a, fin, grid, st);
-    }
-  }
+  const bool any = a.r > 256 || a.long_only || wide_prior;
   // as many tiles of 16 sequences per workgroup as the call has, at most four: the weights are
   // read once per workgroup row
-#define DLS_VOCAB(MT)                                                                                          return a.r <= 128 ? launch_vocab_k<WT, LT, MT, K1, SPL, SAMPLE>(a, fin, dim3(gx, (unsigned)((mt + MT - 1) / MT)), st)                     : launch_vocab_k<WT, LT, MT, K2, SPL, SAMPLE>(a, fin, dim3(gx, (unsigned)((mt + MT - 1) / MT)), st)
-  if (mt == 1) DLS_VOCAB(1);
-  if (mt == 2) DLS_VOCAB(2);
-  DLS_VOCAB(4);
+  const int MT = mt == 1 ? 1 : (mt == 2 || any) ? 2 : 4;
+  dim3 grid((unsigned)a.G, (unsigned)((mt + MT - 1) / MT));
+  // A workgroup writes one row of results at its end.  Where CUs are idle, or sequences more than
+  // workgroups, further workgroups do (Markov head, 48 sequences, V = 2,053 with its 17 workgroups: 389 us a
+  // block with three rows after one another, 195 with a workgroup for each).
+  if (a.finish && (a.batch > a.G || a.G * (int)grid.y + a.batch <= kMaxG)) {
+    a.finish = 2;
+    grid.x += ((unsigned)a.batch + grid.y - 1) / grid.y;
+  }
+  if (any) {
+    const int nkb = (a.r + 8 * Op<WT>::KCH - 1) / (8 * Op<WT>::KCH);
+    return MT == 1 ? launch_vocab_any<WT, LT, 1, SPL, SAMPLE>(a, fin, nkb, grid, st)
+                   : launch_vocab_any<WT, LT, 2, SPL, SAMPLE>(a, fin, nkb, grid, st);
+  }
+#define DLS_VOCAB(MT, PACKED)                                                          \
+  return a.r <= 128 ? launch_vocab_k<WT, LT, MT, K1, SPL, SAMPLE, PACKED>(a, fin, grid, st) \
+                    : launch_vocab_k<WT, LT, MT, K2, SPL, SAMPLE, PACKED>(a, fin, grid, st)
+  if constexpr (sizeof(WT) == 2) {
+    if (a.wv) {   // prepared heads come with r = 128 or 256 and more than 16 sequences (a Markov head: 32)
+      if constexpr (SPL > 1) {
+        if (MT == 2) DLS_VOCAB(2, true);
+      }
+      DLS_VOCAB(4, true);
+    }
+  }
+  if (MT == 1) DLS_VOCAB(1, false);
+  if (MT == 2) DLS_VOCAB(2, false);
+  DLS_VOCAB(4, false);
 #undef DLS_VOCAB
 }
 
