@@ -391,7 +391,6 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
   }
 
   const dls_local_head ch = canon(*head);
-  // the persistent kernel runs at most kMaxBatch sequences per launch (below)
   const dls::PersistWorkspace pw = dls::persist_workspace(ch, std::min<int32_t>(batch, dls::kMaxBatch), B);
   // adaptive fusion: the gates of all batch * B rows first, stream-ordered before the draft
   if (rule) {
@@ -426,8 +425,7 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
   a.unc = out_unc;
   if (head->prepared) {
     // The prepared form is used where the persistent kernel's plan holds for the call, kMaxBatch
-    // sequences at a time: by that kernel up to persist_batch sequences, by the launches per
-    // position above.
+    // sequences at a time: by that kernel or by launches per position (persist_route).
     const int nfull = std::min<int32_t>(batch, dls::kMaxBatch);
     const int nlast = batch - (batch - 1) / dls::kMaxBatch * dls::kMaxBatch;   // the last launch's sequences
     const dls::PersistPlan pl = dls::persist_plan(ch, nfull, B, long_dtype, prior != nullptr, persist_groups(cus));
@@ -448,7 +446,7 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
       expect.w_ih = ch.w_ih;
       expect.w_hh = ch.w_hh;
       expect.w_vocab = ch.w_vocab;
-      if (batch > dls::persist_batch(ch.kind == DLS_HEAD_MARKOV)) {
+      if (!dls::persist_route(ch, pl, batch, B, long_dtype, smp.inv_temp != 0.f)) {
         a.T = ch.kind == DLS_HEAD_MARKOV ? nullptr : (const float*)(pp + PL.off_T);
         a.wv = (const uint4*)(pp + PL.off_wv);
         a.whh = (const uint4*)(pp + PL.off_whh);

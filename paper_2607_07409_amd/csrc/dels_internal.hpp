@@ -117,13 +117,6 @@ hipError_t launch_unigram_prior(const int32_t* tokens, int64_t n, int32_t V, flo
 // prepared heads and the persistent drafting kernel
 // ------------------------------------------------------------------------------------------
 constexpr int kMaxBatch = 64;              // sequences of one plan of the persistent kernel
-// Prepared heads of more sequences than this are drafted by the launches per position.  The persistent
-// kernel's position costs one chain of hand-offs per 16 sequences, the launches' little more for 64
-// than for 16.  At V = 151,936, H = 1,024, r = 256 (us a block, persistent and launches): 64 sequences
-// 993 and 679; 32 535 and 525 (sampled 612 and 565, with the prior 538 and 542); 17 511 and 497
-// (sampled 592 and 540); 20 with r = 128 575 and 445; 28 sampled at V = 100,003 724 and 511.  A Markov
-// head's chain is shorter (no GRU, no rank stage): 32 sequences 348 and 395, 17 sequences 331 and 370.
-inline int persist_batch(bool markov) { return markov ? 32 : 16; }
 constexpr int kMaxG = 256;                 // workgroups (one per CU of a gfx950)
 constexpr size_t kMaxLds = 160 * 1024;     // LDS per CU on gfx950
 constexpr int kNarrowBatch = 4;            // the persistent kernel's narrow form: at most 4 sequences
@@ -198,6 +191,8 @@ struct PersistWorkspace {
 __host__ __device__ inline void persist_tile_range(int w, int G, int NG, int NT, int cap_a, int gcap, int* t0,
                                                    int* n);
 PersistPlan persist_plan(const dls_local_head& h, int32_t batch, int32_t B, dls_dtype long_dtype, bool prior, int G);
+bool persist_route(const dls_local_head& h, const PersistPlan& pl, int32_t batch, int32_t B, dls_dtype long_dtype,
+                   bool sample);   // a prepared call by the persistent kernel rather than by launches per position
 PersistWorkspace persist_workspace(const dls_local_head& h, int32_t batch, int32_t B);
 hipError_t launch_persistent(const PersistArgs& pa, const PersistPlan& pl, dls_dtype long_dtype, hipStream_t st);
 

@@ -84,6 +84,28 @@ PersistPlan persist_plan(const dls_local_head& h, int32_t batch, int32_t B, dls_
   return pl;
 }
 
+// The persistent kernel's position costs one chain of hand-offs per 16 sequences, that of the launches per
+// position little more for 64 than for 16; its block begins by loading the weights (about 20 us, the launches' 4).
+// us a block of 16 positions, persistent and launches, r = 256 unless said otherwise:
+//   RNN H = 1,024, V = 151,936: 17 sequences 510 and 489 (sampled 589 and 542), 32 537 and 520, 64 984 and 678;
+//     V = 64,000 32 sequences 521 and 400
+//   Markov, V = 151,936: 17 sequences 331 and 370, 32 348 and 395, 48 498 and 489, 64 661 and 501
+// With an unaligned vocabulary, or one whose tiles do not fill every workgroup's AGPRs, it loses more (Markov, 33
+// sequences, V = 120,011: 581 and 422; RNN, H = 512, V = 120,011, 17 sequences: 520 and 443).  Where both hold and the
+// chain is short it wins somewhat beyond 16 and 32:
+//   RNN H = 512: V = 151,936 17 sequences 457 and 480, with the prior 460 and 491, float32 logits 475 and 519, 32
+//     sequences 476 and 510 (sampled 552 and 550), V = 131,072 428 and 441; 4, 8, 12 positions of 24 sequences
+//     132 and 126, 244 and 246, 356 and 367
+//   Markov: V = 131,072 33 sequences 415 and 426 (sampled 492 and 523), V = 151,936 48 sequences sampled 588 and 608,
+//     V = 240,000 with r = 128 40 sequences 557 and 566 (sampled 690 and 749); 4 and 8 positions 130 and 124, 245 and 246
+bool persist_route(const dls_local_head& h, const PersistPlan& pl, int32_t batch, int32_t B, dls_dtype long_dtype,
+                   bool sample) {
+  const bool markov = h.kind == DLS_HEAD_MARKOV;
+  if (batch <= (markov ? 32 : 16)) return true;
+  const bool fills = pl.NT > pl.cap_a * pl.G && (size_t)h.V * (long_dtype == DLS_BF16 ? 2 : 4) % 16 == 0 && B >= 8;
+  return fills && (markov ? batch <= 48 : batch <= 32 && h.H <= 512 && h.r == 256 && !sample);
+}
+
 PersistWorkspace persist_workspace(const dls_local_head& h, int32_t batch, int32_t B) {
   PersistWorkspace L;
   size_t o = 256;                                     // header: epoch, error word
