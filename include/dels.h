@@ -184,21 +184,22 @@ dls_status dls_combine_logits(const void *long_logits, const void *short_logits,
  * One draft block per sequence (Algorithm 1, the decoding loop).
  * Two implementations share this entry point.  With head->prepared set and a supported
  * shape (bf16 head, H/16 <= number of CUs, r divisible by H/16 with at most 16 rank rows
- * per group, and the per-CU share of W_vocab fitting in AGPRs + LDS) a call of up to 32
- * sequences runs in one persistent kernel that keeps the head weights on chip for the whole
- * block, and a larger one as a chain of launches per position that reads the prepared form;
- * otherwise the chain reads the head as it is (a head of at most 1 MiB of weights drafts the
- * whole block in one launch).  Sampling keys its noise by each sequence's index in the call,
+ * per group, and the per-CU share of W_vocab fitting in AGPRs + LDS) a call of up to 16
+ * sequences (a Markov head: 32, for some shapes twice and 1.5 times as many) runs in one
+ * persistent kernel that keeps the head weights on chip for the whole block, and a larger
+ * one as a chain of launches per position that reads the prepared form; otherwise the chain
+ * reads the head as it is (a small head drafts the whole block in one launch).  Sampling keys its noise by each sequence's index in the call,
  * so the route does not change a draw.
  * dls_draft_block_path tells which is used.
  * The workspace must be zero-filled before its first use; the library keeps it
- * consistent afterwards.  A persistent call that fails sets the workspace's error word
- * (read it with dls_draft_block_error; the call itself has returned DLS_OK long before,
- * since it only enqueues work).  A failed call writes token -1 at every position it did
+ * consistent afterwards.  A call by the prepared form that fails sets the workspace's error
+ * word (read it with dls_draft_block_error; the call itself has returned DLS_OK long
+ * before, since it only enqueues work).  A failed call writes token -1 at every position it did
  * not finish drafting (all positions unless only the statistics failed) and NaN into
  * every statistics row it could not merge, so that no stale output passes for a draft.
- * Later persistent calls on a workspace whose error word is set do nothing but write
- * the same sentinels, until the workspace is zero-filled again.
+ * Later calls by the prepared form on a workspace whose error word is set write nothing
+ * but the same sentinels, until the workspace is zero-filled again; one whose prepared
+ * buffer is another head's sets the word to DLS_DRAFT_ERR_PREPARED, whatever it held.
  *   head         RNN or Markov local head (see dls_local_head); device pointers
  *   long_logits  [batch, B, V] of `long_dtype`; row j is the long logits of draft
  *                position j
@@ -212,9 +213,9 @@ dls_status dls_combine_logits(const void *long_logits, const void *short_logits,
  * Limits: 1 <= batch <= 256, 1 <= B <= 64 (0 is a no-op), the head limits above,
  * long_dtype F32 or BF16. */
 size_t dls_draft_block_workspace_size(const dls_local_head *head, int32_t batch, int32_t B);
-/* 1: the prepared form would be used for these arguments (the persistent kernel, or above 32
- * sequences the launches per position), 0: launches that read the head as it is,
- * negative: the arguments are invalid.  Needs the device (it counts its CUs). */
+/* 1: the prepared form would be used for these arguments (by the persistent kernel or by the
+ * launches per position), 0: launches that read the head as it is, negative: the arguments
+ * are invalid.  Needs the device (it counts its CUs). */
 int dls_draft_block_path(const dls_local_head *head, int32_t batch, int32_t B, dls_dtype long_dtype,
                          int has_prior);
 dls_status dls_draft_block(const dls_local_head *head, const void *long_logits,
@@ -223,7 +224,7 @@ dls_status dls_draft_block(const dls_local_head *head, const void *long_logits,
                            dls_row_stats *out_stats, void *workspace, size_t ws_bytes,
                            void *stream);
 
-/* Error word of a drafting workspace (0 when every persistent call on it succeeded). */
+/* Error word of a drafting workspace (0 when every call by the prepared form succeeded). */
 #define DLS_DRAFT_ERR_STALLED 1   /* a hand-off between workgroups did not arrive within the spin
                                      budget (about a second): typically other kernels held compute
                                      units during a DLS_EXCLUSIVE_DEVICE call */

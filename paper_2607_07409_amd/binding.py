@@ -255,7 +255,8 @@ class LocalHead:
         return LocalHead(self.emb, self.w_ih, self.w_hh, self.w_rank, self.w_vocab)
 
     def path(self, batch: int, B: int, long_dtype=torch.bfloat16, has_prior=False) -> int:
-        """1 if dls_draft_block would use the persistent kernel, 0 for per-position launches."""
+        """1 if dls_draft_block would use the prepared form (by the persistent kernel or by launches per
+        position), 0 for launches that read the head as it is."""
         code = DLS_BF16 if long_dtype == torch.bfloat16 else DLS_F32
         return int(lib().dls_draft_block_path(ctypes.byref(self.c), batch, B, code, int(bool(has_prior))))
 

@@ -447,7 +447,7 @@ __global__ __launch_bounds__(kST, 2) void k_gates(GatesArgs<WT> a) {
   }
 }
 
-// A prepared buffer of another head sets the error word (an earlier one stays).
+// A prepared buffer of another head sets the error word, whatever it held (as the persistent kernel does).
 __global__ void k_check_prepared(const PreparedHeader* prep, PreparedHeader ex, uint32_t* hdr) {
   const bool same = prep->magic == ex.magic && prep->V == ex.V && prep->d == ex.d && prep->H == ex.H && prep->r == ex.r &&
                     prep->emb == ex.emb && prep->w_ih == ex.w_ih && prep->w_hh == ex.w_hh && prep->w_vocab == ex.w_vocab;

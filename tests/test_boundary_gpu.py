@@ -75,6 +75,20 @@ def test_prepared_buffer_of_another_head_is_refused(i):
     assert B.workspace_error(ws2) == 0 and B.workspace_error(ws) == 0
 
 
+@pytest.mark.parametrize("i", range(len(SHAPES)))
+def test_foreign_buffer_on_a_stalled_workspace(i):
+    """Both routes report the later cause: a foreign prepared buffer over a stalled call's word."""
+    wl, head, lt, last = _setup(i)
+    _, other, _, _ = _setup(i, seed=991)
+    other.c.prepared = head.prepared.data_ptr()
+    other.c.prepared_bytes = head.prepared.numel()
+    ws = B.draft_workspace(head, wl.batch, wl.B)
+    ws[4:8].view(torch.int32).fill_(B.DLS_DRAFT_ERR_STALLED)
+    tok, st = _call(other, lt, last, ws)
+    assert bool((tok == -1).all().item()) and bool(torch.isnan(st).all().item())
+    assert B.workspace_error(ws) == B.DLS_DRAFT_ERR_PREPARED
+
+
 @pytest.mark.parametrize("markov,prepared,batch,adaptive", [
     (False, True, 17, False), (True, True, 33, False), (False, True, 20, True), (False, False, 17, False),
     (True, False, 3, True), (False, True, 3, True)])
