@@ -1,7 +1,7 @@
 // One DeLS-Spec draft block per sequence (Algorithm 1, the decoding loop) as a chain of
 // launches per draft position j, for heads that are drafted with as they are:
 //
-//   k_gates   tokens u_j (argmax keys of position j-1), x = E[u_j], GRU cell -> h
+//   k_gates   (k_gates_rows, k_gates_folded) tokens u_j (argmax keys of position j-1), x = E[u_j], GRU cell -> h
 //   k_rank    rho = SiLU(W_rank h); further workgroups write the results of position j-1
 //   k_vocab   l_S = W_vocab rho, fused with the long logits, online LSEs, top-2; one argmax
 //             key and one partial per (sequence, workgroup)
@@ -10,7 +10,7 @@
 // workgroup gets the tokens and stages their rows itself.  The decoded token never leaves the
 // device and no launch waits for another one beyond the order of the stream.
 //
-// All products run on the matrix cores, 16 weight rows by 16 sequences at a time, with float32
+// The products run on the matrix cores (those of the GRU cell and of W_rank from five sequences on), 16 weight rows by 16 sequences at a time, with float32
 // accuracy (V = 151,936, d = 4,096, H = 1,024, r = 256, 32 sequences, 16 positions in bf16: 749 us a
 // block; one wave per weight row with vector instructions, four sequences at a time, took 10.5 ms,
 // and its error against float64 was larger): a float32 activation is split exactly into three bf16 values of 8 significant bits
@@ -447,6 +447,106 @@ __global__ __launch_bounds__(kST, 2) void k_gates(GatesArgs<WT> a) {
   }
 }
 
+// GRU cell of up to four sequences, where a sixteenth to a quarter of the matrix cores' columns would count: one
+// wave per hidden unit reads its six weight rows in memory order, 1 KB per instruction, those of W_ih kU
+// pieces ahead of the tokens and of their use.  k_gates reads 16 rows at the same columns per instruction, which
+// meet in one memory channel where the row length is a large power of two.  us a block of 16 positions by k_gates and
+// k_rank and by the row kernels (batch 1 / 4): d = 4,096, H = 1,024, V = 151,936, r = 256, bf16 530 / 545 and
+// 496 / 555; d = 4,096, H = 512, float32 554 / 566 and 365 / 422; d = 16,384, H = 64, float32 1,070 / 1,168 and
+// 416 / 628; d = 512, H = 4,096, bf16 1,050 / 1,096 and 497 / 634; d = 128, H = 256, bf16 329 / 338 and 259 / 295.
+constexpr int kRT = 256;
+template <typename WT, int NB>
+__global__ __launch_bounds__(kRT) void k_gates_rows(GatesArgs<WT> a) {
+  constexpr int N = Op<WT>::NP, kU = 4;
+  __shared__ int s_tok[kRT / 64];
+  static_assert(NB <= kRT / 64, "a wave merges the keys of one sequence");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int d = a.d, H = a.H;
+  const int k = min((int)blockIdx.x * (kRT / 64) + wave, H - 1);   // past H: the last unit again, not stored
+  TokenKeys<1> tk;
+  load_keys(a.ts, 0, a.batch, wave, lane, tk);
+  asm volatile("" ::: "memory");
+  float acc[4][NB];   // r, z, n from x, n from h
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[0][b] = acc[1][b] = acc[2][b] = acc[3][b] = 0.f;
+  auto fma_row = [&](float& s, uint4 w, const float* x) {
+    float wv[N];
+    Chunk<WT>::widen(w, wv);
+#pragma unroll
+    for (int i = 0; i < N; ++i) s = __builtin_fmaf(wv[i], x[i], s);
+  };
+  const int np = d / N, nh = H / N;
+  uint4 w[3][kU];
+  auto load_w = [&](const WT* m, int cols, int n, int p) {   // pieces p + lane, + 64, ..
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+#pragma unroll
+      for (int q = 0; q < 3; ++q)
+        w[q][u] = *reinterpret_cast<const uint4*>(m + (size_t)(q * H + k) * cols + (size_t)min(p + u * 64 + lane, n - 1) * N);
+  };
+  load_w(a.w_ih, d, np, 0);
+  asm volatile("" ::: "memory");
+  merge_keys(tk, a.V, wave, lane, s_tok);
+  __syncthreads();
+  const WT* xr[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) xr[b] = a.emb + (size_t)s_tok[b] * d;
+  for (int p = 0; p < np; p += 64 * kU) {
+    uint4 x[NB][kU];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int u = 0; u < kU; ++u) x[b][u] = *reinterpret_cast<const uint4*>(xr[b] + (size_t)min(p + u * 64 + lane, np - 1) * N);
+    uint4 c[3][kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+#pragma unroll
+      for (int q = 0; q < 3; ++q) c[q][u] = w[q][u];
+    if (p + 64 * kU < np) load_w(a.w_ih, d, np, p + 64 * kU);
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const bool ok = p + u * 64 + lane < np;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        float xv[N];
+        Chunk<WT>::widen(sel4(ok, x[b][u]), xv);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) fma_row(acc[q][b], c[q][u], xv);
+      }
+    }
+  }
+  if (!a.h_zero) {
+    const WT* u0 = a.w_hh + (size_t)k * H;
+#pragma unroll 2
+    for (int p = lane; p < nh; p += 64) {
+      uint4 u[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) u[q] = *reinterpret_cast<const uint4*>(u0 + (size_t)q * H * H + (size_t)p * N);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        const float* hp = a.h_in + (size_t)min(b, a.batch - 1) * H + (size_t)p * N;
+        float hv[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) hv[i] = hp[i];
+        fma_row(acc[0][b], u[0], hv);
+        fma_row(acc[1][b], u[1], hv);
+        fma_row(acc[3][b], u[2], hv);
+      }
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q][b] = wave_sum(acc[q][b]);
+    if (lane == 0 && b < a.batch && (int)blockIdx.x * (kRT / 64) + wave < H) {
+      const float rg = sigmoidf_(acc[0][b]), zg = sigmoidf_(acc[1][b]);
+      const float ng = tanhf_(acc[2][b] + rg * acc[3][b]);
+      const float hp = a.h_zero ? 0.f : a.h_in[(size_t)b * H + k];
+      a.h_out[(size_t)b * H + k] = (1.f - zg) * ng + zg * hp;
+    }
+  }
+}
+
 // A prepared buffer of another head sets the error word, whatever it held (as the persistent kernel does).
 __global__ void k_check_prepared(const PreparedHeader* prep, PreparedHeader ex, uint32_t* hdr) {
   const bool same = prep->magic == ex.magic && prep->V == ex.V && prep->d == ex.d && prep->H == ex.H && prep->r == ex.r &&
@@ -588,6 +688,39 @@ __global__ __launch_bounds__(kST) void k_rank(RankArgs<WT> a, FinishArgs fin) {
 #pragma unroll
     for (int w = 0; w < kSW; ++w) v += red[w][l][row & 3];
     if (b0 + s < a.batch && r0 + row < a.r) a.rho[(size_t)(b0 + s) * a.r + r0 + row] = siluf_(v);
+  }
+}
+
+// The same for a few sequences (batch <= NB): one wave per rank row.
+template <typename WT, int NB>
+__global__ __launch_bounds__(kST) void k_rank_rows(RankArgs<WT> a, FinishArgs fin) {
+  constexpr int N = Op<WT>::NP;
+  __shared__ Partial sh[kSW];
+  if ((int)blockIdx.x >= a.tiles) {   // tiles = ceil(r / kSW)
+    finish_row(fin, blockIdx.x - a.tiles, sh);
+    return;
+  }
+  const int lane = threadIdx.x & 63, i = blockIdx.x * kSW + (threadIdx.x >> 6);
+  if (i >= a.r) return;
+  const WT* wr = a.w_rank + (size_t)i * a.H;
+  float acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[b] = 0.f;
+#pragma unroll 4
+  for (int p = lane; p < a.H / N; p += 64) {
+    float w[N];
+    Chunk<WT>::load(wr + (size_t)p * N, w);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const float* hp = a.h + (size_t)min(b, a.batch - 1) * a.H + (size_t)p * N;
+#pragma unroll
+      for (int e = 0; e < N; ++e) acc[b] = __builtin_fmaf(w[e], hp[e], acc[b]);
+    }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const float s = wave_sum(acc[b]);
+    if (lane == 0 && b < a.batch) a.rho[(size_t)b * a.r + i] = siluf_(s);
   }
 }
 
@@ -1408,6 +1541,7 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
   bool first_head_step = true;
   for (int j = 0; j < B; ++j) {
     const bool long_only = literal && j == 0;
+    const bool rows = !a.T && batch <= 4;   // see k_gates_rows
     TokenSource ts;
     ts.keys = j ? keys + set_of(j - 1) : nullptr;
     ts.last = a.last_token;
@@ -1440,7 +1574,11 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
         ga.h_zero = first_head_step;
         ga.h_out = hn;
         const unsigned gx = (unsigned)((H + kUnits - 1) / kUnits);
-        if (batch <= 16) k_gates<WT, 1><<<dim3(gx, 1), kST, 0, st>>>(ga);
+        const unsigned gr = (unsigned)((H + kRT / 64 - 1) / (kRT / 64));
+        if (batch == 1) k_gates_rows<WT, 1><<<gr, kRT, 0, st>>>(ga);
+        else if (batch == 2) k_gates_rows<WT, 2><<<gr, kRT, 0, st>>>(ga);
+        else if (batch <= 4) k_gates_rows<WT, 4><<<gr, kRT, 0, st>>>(ga);
+        else if (batch <= 16) k_gates<WT, 1><<<dim3(gx, 1), kST, 0, st>>>(ga);
         else if (batch <= 32) k_gates<WT, 2><<<dim3(gx, 1), kST, 0, st>>>(ga);
         else k_gates<WT, 4><<<dim3(gx, (unsigned)((batch + 63) / 64)), kST, 0, st>>>(ga);
       }
@@ -1453,7 +1591,12 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
       ra.tiles = ((r + 15) / 16) * ((batch + 15) / 16);
       ra.h = hn;
       ra.rho = rho;
-      k_rank<WT><<<(unsigned)(ra.tiles + (j ? batch : 0)), kST, 0, st>>>(ra, fin);
+      if (rows) ra.tiles = (r + kSW - 1) / kSW;
+      const unsigned gk = (unsigned)(ra.tiles + (j ? batch : 0));
+      if (!rows) k_rank<WT><<<gk, kST, 0, st>>>(ra, fin);
+      else if (batch == 1) k_rank_rows<WT, 1><<<gk, kST, 0, st>>>(ra, fin);
+      else if (batch == 2) k_rank_rows<WT, 2><<<gk, kST, 0, st>>>(ra, fin);
+      else k_rank_rows<WT, 4><<<gk, kST, 0, st>>>(ra, fin);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       std::swap(hc, hn);
       first_head_step = false;

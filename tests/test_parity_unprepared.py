@@ -38,6 +38,10 @@ CASES = [
     (9973, 0, 0, 120, 5, 9, "f32", "f32", 0.7, False, True, True),
     (8200, 0, 0, 264, 4, 50, "bf16", "bf16", 0.0, True, False, True),
     (520_001, 8, 8, 8, 2, 3, "bf16", "bf16", 0.0, True, False, False),   # the prior's slice exceeds its LDS
+    (20_011, 4104, 264, 72, 3, 2, "bf16", "bf16", 0.0, False, False, False),   # one wave per row: rounds of 2,048
+    (20_011, 1064, 1032, 264, 3, 4, "f32", "f32", 0.7, True, False, False),    # (bf16) or 1,024 columns, a ragged last one
+    (20_011, 2048, 520, 40, 4, 1, "f32", "bf16", 0.0, True, True, False),
+    (20_011, 16, 2056, 136, 3, 3, "bf16", "bf16", 0.0, False, False, False),
 ]
 
 
