@@ -1,7 +1,9 @@
 // One DeLS-Spec draft block per sequence (Algorithm 1, the decoding loop) as a chain of
-// launches per draft position j, for heads that are drafted with as they are:
+// launches per draft position j, for heads that are drafted with as they are and for prepared ones
+// where the persistent kernel is the slower route:
 //
-//   k_gates   (k_gates_rows, k_gates_folded) tokens u_j (argmax keys of position j-1), x = E[u_j], GRU cell -> h
+//   k_gates   tokens u_j (argmax keys of position j-1), x = E[u_j], GRU cell -> h
+//             (k_gates_rows: up to four sequences; k_gates_folded: a prepared head)
 //   k_rank    rho = SiLU(W_rank h); further workgroups write the results of position j-1
 //   k_vocab   l_S = W_vocab rho, fused with the long logits, online LSEs, top-2; one argmax
 //             key and one partial per (sequence, workgroup)
@@ -10,12 +12,12 @@
 // workgroup gets the tokens and stages their rows itself.  The decoded token never leaves the
 // device and no launch waits for another one beyond the order of the stream.
 //
-// The products run on the matrix cores (those of the GRU cell and of W_rank from five sequences on), 16 weight rows by 16 sequences at a time, with float32
-// accuracy (V = 151,936, d = 4,096, H = 1,024, r = 256, 32 sequences, 16 positions in bf16: 749 us a
-// block; one wave per weight row with vector instructions, four sequences at a time, took 10.5 ms,
-// and its error against float64 was larger): a float32 activation is split exactly into three bf16 values of 8 significant bits
-// (bf16 heads, v_mfma_f32_16x16x32_bf16), or multiplied as it is (float32 heads,
-// v_mfma_f32_16x16x4_f32).  Products of bf16 values are exact and the sums are float32.
+// The products run on the matrix cores (those of the GRU cell and of W_rank from five sequences on), 16
+// weight rows by 16 sequences at a time, with float32 accuracy (V = 151,936, d = 4,096, H = 1,024, r = 256, 32
+// sequences, 16 positions in bf16: 739 us a block; one wave per weight row with vector instructions, four
+// sequences at a time, took 10.5 ms, and its error against float64 was larger): a float32 activation is split
+// exactly into three bf16 values of 8 significant bits (bf16 heads, v_mfma_f32_16x16x32_bf16), or multiplied as
+// it is (float32 heads, v_mfma_f32_16x16x4_f32).  Products of bf16 values are exact and the sums are float32.
 #pragma once
 #include <atomic>
 
@@ -776,6 +778,13 @@ __device__ __forceinline__ void push8(Lse& a, const float* x) {
 // a finite-start state without an entry becomes the empty one (a NaN sum is kept)
 __device__ __forceinline__ void close_lse(Lse& a) { a.m = a.s == 0.f ? -INFINITY : a.m; }
 
+// The same for a sum of exp2(x log2(e) + neg), neg = -m log2(e) rounded: the rounding is taken out of the sum
+// (of magnitudes where it is small beside 1).
+__device__ __forceinline__ void close_ref(Lse& a, float neg) {
+  if (fabsf(a.m) < 1.0e6f) a.s *= fast_exp2(-__builtin_fmaf(a.m, kLog2e, neg));
+  close_lse(a);
+}
+
 template <int N>
 struct PermN {   // N consecutive lanes
   template <typename F>
@@ -1256,8 +1265,9 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
 
   // The entries of the step before (long, short, fused; -inf past the vocabulary and the call) are
   // folded while the matrix cores work on this one.  The sums are rescaled to the running maxima as the
-  // entries are made: a reference that lags (moved only when a value lies 40 above it) is 18 us of 682 at
-  // batch 64 faster, but leaves the exponents of the entries that count six bits short after the point.
+  // entries are made, by the difference of the rounded references that the entries use, and the rounding of the
+  // last one is taken out at the end.  References that lag (moved only when a value lies 40 above them) saved 3% of a
+  // batch-64 block, but left the exponents of the entries that count six bits short after the point.
   float x[4], s[4], f[4];
   int vp = 0;
 #pragma unroll
@@ -1270,10 +1280,11 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
     a.s += (e0 + e1) + (e2 + e3);
   };
   auto move_ref = [](Lse& a, float& neg, float m) {   // to the maximum with m
-    const float mn = fmaxf(a.m, m);
-    a.s *= fast_exp2((a.m - mn) * kLog2e);
-    a.m = mn;
-    neg = -mn * kLog2e;
+#pragma clang fp contract(off)   // n - neg as a fused product would miss 0 by the rounding of n
+    a.m = fmaxf(a.m, m);
+    const float n = -a.m * kLog2e;
+    a.s *= fast_exp2(n - neg);   // exactly 1 while the maximum stays
+    neg = n;
   };
   auto fold = [&]() {
     add4(P.L, nl, x);
@@ -1385,9 +1396,9 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
   fold();
 
   // merge: the four row groups of a wave, then the NSTR waves of a sequence tile through LDS
-  close_lse(P.L);
-  close_lse(P.S);
-  close_lse(P.F);
+  close_ref(P.L, nl);
+  close_ref(P.S, ns);
+  close_ref(P.F, nf);
   P = allred_partial(P, Perm4Rows{});
   __syncthreads();
   Partial* sp = reinterpret_cast<Partial*>(smem);   // [str][16 MT]
