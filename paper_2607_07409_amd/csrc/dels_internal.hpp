@@ -105,7 +105,7 @@ struct DraftArgs {
   uint32_t* hdr = nullptr;
 };
 hipError_t launch_draft(const DraftArgs& a, hipStream_t st);
-bool small_head(const dls_local_head& h, int32_t B);   // drafted by one workgroup per sequence
+bool small_head(const dls_local_head& h, int32_t batch, int32_t B);   // drafted by one workgroup per sequence
 hipError_t launch_small(const DraftArgs& a, hipStream_t st);
 
 hipError_t launch_accept(const int32_t* draft, const int32_t* target, int32_t batch, int32_t B,

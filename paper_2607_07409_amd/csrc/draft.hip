@@ -39,7 +39,7 @@ DraftLayout draft_layout(const dls_local_head& h, int32_t batch, int32_t B) {
 }
 
 hipError_t launch_draft(const DraftArgs& a, hipStream_t st) {
-  if (!a.prep && small_head(a.head, a.B)) return launch_small(a, st);
+  if (!a.prep && small_head(a.head, a.batch, a.B)) return launch_small(a, st);
   if (a.head.dtype == DLS_BF16)
     return a.long_dtype == DLS_BF16 ? launch_mode<bf16_t, bf16_t>(a, st) : launch_mode<bf16_t, float>(a, st);
   return a.long_dtype == DLS_BF16 ? launch_mode<float, bf16_t>(a, st) : launch_mode<float, float>(a, st);

@@ -3,8 +3,8 @@
 //
 // A chain of launches costs a few microseconds per launch and position whatever a head's size; one
 // CU reads about 100 KB of weights per microsecond from L2.  A head of up to kSmallBytes of weights
-// (read once per position) is therefore drafted here, larger ones by the chain: at V = 1024, d = H = r
-// = 64 in float32 (368 KB) the chain took 78 us for four positions.
+// (read once per position) is drafted here where small_head expects less time than of the chain: at V = 1024,
+// d = H = r = 64 in float32 (368 KB) 43 us for four positions, by the chain 67.
 //
 // Sixteen lanes share a weight row (16-byte pieces, a DPP sum over the row of lanes), float32
 // throughout.  In the vocabulary phase a group of sixteen lanes takes sixteen rows at a time and lane
@@ -215,11 +215,27 @@ size_t small_lds(const dls_local_head& h, int32_t B) {
 
 }  // namespace
 
-// At most kSmallBytes of weights per position, and vectors and partials within 64 KiB of LDS.
-bool small_head(const dls_local_head& h, int32_t B) {
-  const size_t esz = h.dtype == DLS_BF16 ? 2 : 4;
-  const size_t rnn = h.kind == DLS_HEAD_MARKOV ? 0 : (size_t)3 * h.H * (h.d + h.H) + (size_t)h.r * h.H;
-  return (rnn + (size_t)h.V * h.r) * esz <= kSmallBytes && small_lds(h, B) <= 64 * 1024;
+// At most kSmallBytes of weights per position, vectors and partials within 64 KiB of LDS, and a shorter position
+// here than in the chain, both in tenths of a microsecond.  Here every sixteen pieces of a row (16 bytes a lane) of
+// the 64 units, 64 rank rows or 1,024 vocabulary rows at a time are a round; the chain's launches take longer for
+// more sequences and for float32.  Fitted to both over 480 calls (V 64 to 8,192, d to 8,192, H to 400, r 8 to 512, 1
+// to 256 sequences); the route it takes is within 5% of the better one for 471 of them and within 10% for all.
+// us a block of 16 positions in bf16 at batch 1, here and by the chain: V = 3,072, d = H = r = 64 265 and 261; V =
+// 6,000 431 and 261; V = 60,000, d = H = r = 8 3,210 and 271; V = 64, d = r = 8, H = 400 363 and 249; Markov, r = 64,
+// V = 256 106 and 106, V = 1,024 130 and 113; 64 sequences: V = 6,000 442 and 507, Markov, V = 1,024 132 and 198.
+bool small_head(const dls_local_head& h, int32_t batch, int32_t B) {
+  const bool f32 = h.dtype != DLS_BF16, markov = h.kind == DLS_HEAD_MARKOV;
+  const size_t rnn = markov ? 0 : (size_t)3 * h.H * (h.d + h.H) + (size_t)h.r * h.H;
+  if ((rnn + (size_t)h.V * h.r) * (f32 ? 4 : 2) > kSmallBytes || small_lds(h, B) > 64 * 1024) return false;
+  const int lanes = f32 ? 64 : 128;   // columns of sixteen pieces
+  auto rounds = [&](int n) { return (n + lanes - 1) / lanes; };
+  int here = rounds(h.r) * (10 + (int)((int64_t)30 * h.V / 1024));
+  if (!markov) here += 30 + (h.H + 63) / 64 * (20 + 3 * (rounds(h.d) + rounds(h.H))) + (h.r + 63) / 64 * rounds(h.H);
+  if (f32) here = here * 4 / 5;
+  int chain = markov ? (batch <= 16 ? 25 : batch <= 32 ? 65 : 90) + (h.r > 256 ? 40 : 0)
+                     : (batch <= 4 ? 180 : batch <= 16 ? 195 : batch <= 32 ? 235 : 305) + h.d / (batch <= 4 ? 400 : 128);
+  if (f32) chain = chain * 17 / 10;
+  return here <= chain;
 }
 
 hipError_t launch_small(const DraftArgs& a, hipStream_t st) {

@@ -42,6 +42,12 @@ CASES = [
     (20_011, 1064, 1032, 264, 3, 4, "f32", "f32", 0.7, True, False, False),    # (bf16) or 1,024 columns, a ragged last one
     (20_011, 2048, 520, 40, 4, 1, "f32", "bf16", 0.0, True, True, False),
     (20_011, 16, 2056, 136, 3, 3, "bf16", "bf16", 0.0, False, False, False),
+    (256, 0, 0, 64, 5, 3, "bf16", "bf16", 0.0, True, False, True),             # one workgroup per sequence or launches:
+    (1500, 0, 0, 64, 3, 40, "f32", "bf16", 0.7, False, True, True),            # on either side of that rule
+    (1500, 0, 0, 64, 3, 3, "f32", "bf16", 0.7, False, True, True),
+    (4500, 64, 64, 64, 3, 40, "bf16", "bf16", 0.0, True, True, False),
+    (4500, 64, 64, 64, 3, 2, "bf16", "bf16", 0.0, True, True, False),
+    (40_000, 8, 8, 8, 3, 1, "bf16", "f32", 0.7, False, False, False),
 ]
 
 
