@@ -328,8 +328,12 @@ hipError_t launch_combine_t(const CombineArgs& a, hipStream_t st) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if (a.out_scores) {
-    // about eight workgroups per CU, none without a piece for each of its threads
-    const int64_t per_row = std::max<int64_t>(1, std::min<int64_t>(a.V / (Chunk<T>::N * kThreads), (2048 + a.rows - 1) / a.rows));
+    // About four workgroups per CU; from 256 rows on, where the inputs of the first pass are no longer in the
+    // caches, many short ones instead.  None with less than two pieces for each of its threads.  us a call with 1,024
+    // and with 25,600 workgroups: float32 [600, 70001] 187 and 180, bf16 [400, 151936] 177 and 174; with 2,048, one piece
+    // and more, float32 [16, 151936] 18.4 (1,024: 16.0).
+    const int64_t wgs = a.rows < 256 ? 1024 : 25600;
+    const int64_t per_row = std::max<int64_t>(1, std::min<int64_t>(a.V / (2 * Chunk<T>::N * kThreads), (wgs + a.rows - 1) / a.rows));
     dim3 g2((unsigned)a.rows, (unsigned)per_row);
     k_combine_scores<T, PRIOR, WLONG><<<g2, kThreads, 0, st>>>(
         (const T*)a.long_logits, (const T*)a.short_logits, a.prior, a.V, a.wl, a.al, a.be, a.norm, a.partials, parts,
