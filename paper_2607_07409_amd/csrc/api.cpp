@@ -446,7 +446,7 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
       expect.w_ih = ch.w_ih;
       expect.w_hh = ch.w_hh;
       expect.w_vocab = ch.w_vocab;
-      if (!dls::persist_route(ch, pl, batch, B, long_dtype, smp.inv_temp != 0.f)) {
+      if (!dls::persist_route(ch, pl, batch, B, long_dtype, smp.inv_temp != 0.f, prior != nullptr, out_stats != nullptr)) {
         a.T = ch.kind == DLS_HEAD_MARKOV ? nullptr : (const float*)(pp + PL.off_T);
         a.wv = (const uint4*)(pp + PL.off_wv);
         a.whh = (const uint4*)(pp + PL.off_whh);

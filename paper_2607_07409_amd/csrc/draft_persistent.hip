@@ -95,15 +95,16 @@ PersistPlan persist_plan(const dls_local_head& h, int32_t batch, int32_t B, dls_
 // chain is short it wins somewhat beyond 16 and 32:
 //   RNN H = 512: V = 151,936 17 sequences 457 and 480, with the prior 460 and 491, float32 logits 475 and 519, 32
 //     sequences 476 and 510 (sampled 552 and 550), V = 131,072 428 and 441; 4, 8, 12 positions of 24 sequences
-//     132 and 126, 244 and 246, 356 and 367
+//     132 and 126, 244 and 246, 356 and 367; H = 1,024 for tokens alone with the prior, 17 and 32 sequences 470 and 482,
+//     507 and 503
 //   Markov: V = 131,072 33 sequences 415 and 426 (sampled 492 and 523), V = 151,936 48 sequences sampled 588 and 608,
 //     V = 240,000 with r = 128 40 sequences 557 and 566 (sampled 690 and 749); 4 and 8 positions 130 and 124, 245 and 246
 bool persist_route(const dls_local_head& h, const PersistPlan& pl, int32_t batch, int32_t B, dls_dtype long_dtype,
-                   bool sample) {
+                   bool sample, bool prior, bool stats) {
   const bool markov = h.kind == DLS_HEAD_MARKOV;
   if (batch <= (markov ? 32 : 16)) return true;
   const bool fills = pl.NT > pl.cap_a * pl.G && (size_t)h.V * (long_dtype == DLS_BF16 ? 2 : 4) % 16 == 0 && B >= 8;
-  return fills && (markov ? batch <= 48 : batch <= 32 && h.H <= 512 && h.r == 256 && !sample);
+  return fills && (markov ? batch <= 48 : batch <= 32 && h.H <= (prior && !stats ? 1024 : 512) && h.r == 256 && !sample);
 }
 
 PersistWorkspace persist_workspace(const dls_local_head& h, int32_t batch, int32_t B) {

@@ -747,6 +747,7 @@ struct VocabArgs {
   const dls_row_uncertainty* unc;
   uint64_t* keys;
   StepPart* parts;
+  int stats;                     // log-sum-exps are wanted
   int finish;                    // the results of the position before are written by: 0 nobody, 1 the workgroups,
                                  // at their end, 2 further workgroups (blockIdx.x >= G)
 };
@@ -1130,7 +1131,10 @@ struct VocabPlan {
 };
 
 // PACKED: the weights are in operand order already (KC chunks a tile), else rows of r columns.
-template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED>
+// STATS: with the log-sum-exps; a call for tokens alone goes without (prepared heads, where it matters beside the
+// persistent kernel, which does so too: batch 64 at V = 151,936, r = 256 590 us a block, with them 676; a uniform branch
+// instead costs sampled calls with statistics 3%).
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED, bool STATS>
 __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArgs fin) {
   using O = Op<WT>;
   using PL = VocabPlan<MT, KC>;
@@ -1287,9 +1291,11 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
     neg = n;
   };
   auto fold = [&]() {
-    add4(P.L, nl, x);
-    add4(P.S, ns, s);
-    add4(P.F, nf, f);
+    if (STATS) {
+      add4(P.L, nl, x);
+      add4(P.S, ns, s);
+      add4(P.F, nf, f);
+    }
     float y[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = f[e];
@@ -1363,9 +1369,11 @@ __global__ __launch_bounds__(kST, 2) void k_vocab(VocabArgs<WT, LT> a, FinishArg
         f[e] = in ? f[e] : -INFINITY;
       }
     }
-    move_ref(P.L, nl, max4(x));
-    move_ref(P.S, ns, max4(s));
-    move_ref(P.F, nf, max4(f));
+    if (STATS) {
+      move_ref(P.L, nl, max4(x));
+      move_ref(P.S, ns, max4(s));
+      move_ref(P.F, nf, max4(f));
+    }
   };
   auto step = [&](int u, int i) {
     const int t = T0 + (rev ? steps - 1 - i : i) * NSTR + str;
@@ -1451,16 +1459,24 @@ hipError_t launch_vocab_any(const VocabArgs<WT, LT>& a, const FinishArgs& fin, i
   return hipGetLastError();
 }
 
-template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED>
-hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
-  auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>;
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED, bool STATS>
+hipError_t launch_vocab_s(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
+  auto kern = k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED, STATS>;
   // the final merge takes 128 partials
   const size_t lds = std::max({VocabPlan<MT, KC>::kLds + (a.prior ? kPriorTiles * 64 : 0), VocabPlan<MT, KC>::act(SPL),
                                128 * sizeof(Partial)});
-  hipError_t e = raise_lds_limit<k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED>>(lds);
+  hipError_t e = raise_lds_limit<k_vocab<WT, LT, MT, KC, SPL, SAMPLE, PACKED, STATS>>(lds);
   if (e != hipSuccess) return e;
   kern<<<grid, kST, lds, st>>>(a, fin);
   return hipGetLastError();
+}
+
+template <typename WT, typename LT, int MT, int KC, int SPL, bool SAMPLE, bool PACKED>
+hipError_t launch_vocab_k(const VocabArgs<WT, LT>& a, const FinishArgs& fin, dim3 grid, hipStream_t st) {
+  if constexpr (PACKED) {
+    if (!a.stats) return launch_vocab_s<WT, LT, MT, KC, SPL, SAMPLE, PACKED, false>(a, fin, grid, st);
+  }
+  return launch_vocab_s<WT, LT, MT, KC, SPL, SAMPLE, PACKED, true>(a, fin, grid, st);
 }
 
 template <typename WT, typename LT, int SPL, bool SAMPLE>
@@ -1636,6 +1652,7 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     va.unc = a.unc;
     va.keys = keys + set_of(j);
     va.parts = parts + set_of(j);
+    va.stats = a.out_stats != nullptr;
     va.finish = markov && j;
     e = markov ? launch_vocab<WT, LT, 1, SAMPLE>(va, fin, st) : launch_vocab<WT, LT, Op<WT>::SPL, SAMPLE>(va, fin, st);
     if (e != hipSuccess) return e;

@@ -143,6 +143,8 @@ def test_prepared_heads_of_many_sequences(V, r, batch, T, markov, literal):
     torch.cuda.synchronize()
     assert B.workspace_error(ws) == 0
     assert torch.equal(tok, again[0]) and torch.equal(st.view(torch.int32), again[1].view(torch.int32))
+    alone, none = B.draft_block(*args, want_stats=False, **kw)   # tokens alone: the kernel without log-sum-exps
+    assert none is None and torch.equal(alone, tok) and B.workspace_error(ws) == 0
     rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, prior, 1.0, al, be, literal,
                       temperature=T, seed=5)
     assert all(e < 2e-4 for e in rep["errs"].values()), rep["errs"]
