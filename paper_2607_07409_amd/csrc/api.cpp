@@ -354,7 +354,6 @@ dls_status draft_impl(const dls_local_head* head, const void* long_logits, int l
   smp.temp = T > 0.f ? T : 1.f;
   smp.seed_lo = (uint32_t)sampling.seed;
   smp.seed_hi = (uint32_t)(sampling.seed >> 32);
-  smp.b0 = 0;
   const bool literal = (fusion.flags & DLS_FIRST_ROW_LONG_ONLY) != 0;
   if (!long_logits || !out_tokens || (!last_token && !literal))
     return fail(DLS_ERR_ARG, "required pointer is NULL");

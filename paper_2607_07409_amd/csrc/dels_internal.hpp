@@ -191,8 +191,9 @@ struct PersistWorkspace {
 __host__ __device__ inline void persist_tile_range(int w, int G, int NG, int NT, int cap_a, int gcap, int* t0,
                                                    int* n);
 PersistPlan persist_plan(const dls_local_head& h, int32_t batch, int32_t B, dls_dtype long_dtype, bool prior, int G);
+// a prepared call by the persistent kernel (true) or by launches per position
 bool persist_route(const dls_local_head& h, const PersistPlan& pl, int32_t batch, int32_t B, dls_dtype long_dtype,
-                   bool sample, bool prior, bool stats);   // a prepared call by the persistent kernel rather than by launches per position
+                   bool sample, bool prior, bool stats);
 PersistWorkspace persist_workspace(const dls_local_head& h, int32_t batch, int32_t B);
 hipError_t launch_persistent(const PersistArgs& pa, const PersistPlan& pl, dls_dtype long_dtype, hipStream_t st);
 

@@ -211,7 +211,8 @@ struct TokenKeys {
   uint64_t k[NS][kMaxG / 64];
 };
 template <int NS>
-__device__ __forceinline__ void load_keys(const TokenSource& ts, int b0, int batch, int wave, int lane, TokenKeys<NS>& tk) {
+__device__ __forceinline__ void load_keys(const TokenSource& ts, int b0, int batch, int wave, int lane,
+                                          TokenKeys<NS>& tk) {
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     const int b = min(b0 + wave + s * kSW, batch - 1);
@@ -550,6 +551,7 @@ __global__ __launch_bounds__(kRT) void k_gates_rows(GatesArgs<WT> a) {
 }
 
 // A prepared buffer of another head sets the error word, whatever it held (as the persistent kernel does).
+template <typename WT>   // bf16_t
 __global__ void k_check_prepared(const PreparedHeader* prep, PreparedHeader ex, uint32_t* hdr) {
   const bool same = prep->magic == ex.magic && prep->V == ex.V && prep->d == ex.d && prep->H == ex.H && prep->r == ex.r &&
                     prep->emb == ex.emb && prep->w_ih == ex.w_ih && prep->w_hh == ex.w_hh && prep->w_vocab == ex.w_vocab;
@@ -569,8 +571,9 @@ struct FoldedArgs {
   int h_zero;
   float* h_out;
 };
+template <typename WT>   // bf16_t: a template, so that only the units of bf16 heads hold it
 __global__ __launch_bounds__(kST, 2) void k_gates_folded(FoldedArgs a) {
-  using O = Op<bf16_t>;
+  using O = Op<WT>;
   constexpr int NB = 4;   // chunks in flight
   __shared__ int s_tok[16];
   __shared__ f32x4_t red[kSW][3][64];
@@ -618,7 +621,7 @@ __global__ __launch_bounds__(kST, 2) void k_gates_folded(FoldedArgs a) {
           const float4 v[2] = {make_float4(x[i][0].x, x[i][0].y, x[i][0].z, x[i][0].w),
                                make_float4(x[i][1].x, x[i][1].y, x[i][1].z, x[i][1].w)};
           uint4 sp[O::SPL];
-          act_split<bf16_t>(v, true, sp);
+          act_split<WT>(v, true, sp);
 #pragma unroll
           for (int e = O::SPL - 1; e >= 0; --e)
 #pragma unroll
@@ -852,10 +855,8 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
     }
     if (!a.long_only) load_w(t, p, 0);
   };
-  // two pairs in flight where the registers allow
-  constexpr bool DEEP = false;
   const bool rfull = r == nkb * KCB * O::KCH;
-  Pair t0, t1;
+  Pair t0;
 
   // activations of the 16 MT sequences as operands in LDS: [m][chunk][split][lane] of 16 bytes.
   // Loads return in order: the activations are asked for before the weights, which then arrive
@@ -884,7 +885,6 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
       const uint4 o = sel4(piece_ok(i), *reinterpret_cast<const uint4*>(a.e_m + (size_t)s_tok[i / (kc * 4)] * r + piece_col(i)));
       put(i, &o);
     }
-    if (DEEP) load_pair(t1, p0 + 1);
   } else {
     float4 v[NQ][NF];
     const float* rho0 = a.rho;
@@ -899,7 +899,6 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
       asm volatile("" ::: "memory");
     }
     load_pair(t0, p0);
-    if (DEEP) load_pair(t1, p0 + 1);
     if (!a.long_only) {
       asm volatile("" ::: "memory");
 #pragma unroll
@@ -934,7 +933,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
     beb[m] = a.be * gt;
   }
 
-  auto process = [&](Pair& t, int p, int ahead) {
+  auto process = [&](Pair& t, int p) {
     const int v0 = kPairRows * p + 8 * g;
     const bool whole = kPairRows * (p + 1) <= V;   // uniform
     float pr[8];
@@ -973,7 +972,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
         }
       }
     }
-    load_pair(t, p + ahead);   // in flight during the fold
+    load_pair(t, p + 1);   // in flight during the fold
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
       float x[8], s[8], f[8];
@@ -1028,14 +1027,7 @@ __global__ __launch_bounds__(kST, 2) void k_vocab_any(VocabArgs<WT, LT> a, Finis
       for (int e = 0; e < 8; ++e) top2_push(P[m], f[e], v0 + e);
     }
   };
-  if (DEEP) {
-    for (int p = p0; p < p1; p += 2) {
-      process(t0, p, 2);
-      if (p + 1 < p1) process(t1, p + 1, 2);
-    }
-  } else {
-    for (int p = p0; p < p1; ++p) process(t0, p, 1);
-  }
+  for (int p = p0; p < p1; ++p) process(t0, p);
 
   // merge: the four row groups of a wave, then the eight waves through LDS
   __syncthreads();
@@ -1561,8 +1553,8 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     f.hdr = a.hdr;
     return f;
   };
-  if (a.prep) {
-    k_check_prepared<<<1, 1, 0, st>>>(a.prep, *a.expect, a.hdr);
+  if constexpr (sizeof(WT) == 2) {   // prepared heads are bf16
+    if (a.prep) k_check_prepared<WT><<<1, 1, 0, st>>>(a.prep, *a.expect, a.hdr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   bool first_head_step = true;
@@ -1575,19 +1567,22 @@ hipError_t launch_step(const DraftArgs& a, hipStream_t st) {
     ts.G = G;
     const FinishArgs fin = finish_of(j ? j - 1 : 0);
     if (!long_only && !markov) {
-      if (a.T) {
-        FoldedArgs fa;
-        fa.T = a.T;
-        fa.whh = a.whh;
-        fa.H = H;
-        fa.V = V;
-        fa.batch = batch;
-        fa.ts = ts;
-        fa.h_in = hc;
-        fa.h_zero = first_head_step;
-        fa.h_out = hn;
-        k_gates_folded<<<dim3((unsigned)(H / 16), (unsigned)((batch + 15) / 16)), kST, 0, st>>>(fa);
-      } else {
+      if constexpr (sizeof(WT) == 2) {
+        if (a.T) {
+          FoldedArgs fa;
+          fa.T = a.T;
+          fa.whh = a.whh;
+          fa.H = H;
+          fa.V = V;
+          fa.batch = batch;
+          fa.ts = ts;
+          fa.h_in = hc;
+          fa.h_zero = first_head_step;
+          fa.h_out = hn;
+          k_gates_folded<WT><<<dim3((unsigned)(H / 16), (unsigned)((batch + 15) / 16)), kST, 0, st>>>(fa);
+        }
+      }
+      if (!a.T) {
         GatesArgs<WT> ga;
         ga.emb = (const WT*)hd.emb;
         ga.w_ih = (const WT*)hd.w_ih;
