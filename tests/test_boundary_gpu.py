@@ -1,11 +1,12 @@
-"""Failure handling of the persistent drafting kernel through the C ABI, forced from the host so
-that every kernel exits normally at its entry check:
+"""Failure handling of prepared drafting calls through the C ABI, by the persistent kernel and by the launches
+per position, forced from the host so that every kernel exits normally:
 
 * a workspace whose error word is already set (an earlier stalled hand-off) makes a call write
   token -1 everywhere and NaN statistics, and dls_draft_block_error reports the word; a
   zero-filled workspace works again;
 * a prepared buffer that belongs to another head (same shapes, other tensors) is refused by
-  the kernel (DLS_DRAFT_ERR_PREPARED) with the same sentinels; the error word is sticky.
+  the kernels (DLS_DRAFT_ERR_PREPARED) with the same sentinels; the error word is sticky;
+* no route leaves words in a workspace that another one could take for its own.
 """
 import numpy as np
 import pytest
@@ -16,8 +17,9 @@ from paper_2607_07409_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [dict(V=5003, d=96, H=128, r=128, B=7, batch=3),      # narrow kernel
-          dict(V=4099, d=128, H=128, r=128, B=5, batch=37)]    # wide kernel (three M tiles)
+SHAPES = [dict(V=5003, d=96, H=128, r=128, B=7, batch=3),      # persistent kernel, narrow
+          dict(V=4099, d=128, H=128, r=128, B=5, batch=37),    # launches per position
+          dict(V=4099, d=128, H=128, r=128, B=5, batch=11)]    # persistent kernel, wide
 
 
 def _setup(i, seed=None):

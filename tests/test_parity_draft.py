@@ -125,7 +125,7 @@ def test_serving_b16(init, prepared):
 
 @pytest.mark.parametrize("prepared", [False, True])
 def test_serving_b64(prepared):
-    """Every sequence of the batch-64 workload (four 16-sequence M tiles of the wide kernel)."""
+    """Every sequence of the batch-64 workload (launches per position, four tiles of 16 sequences a workgroup)."""
     p = _problem("b64-d5120", "stress")
     _check(p, 0.5, prepared=prepared)
 
@@ -142,8 +142,8 @@ def test_serving_b64_prior(prepared):
 @pytest.mark.parametrize("name", ["qwen3-4b-b1", "qwen3-8b-b16", "b64-d5120"])
 def test_masked_long_logits(name, w_long, prepared):
     """-inf long logits (masked tokens, allowed by the ABI) through dls_draft_block, every sequence:
-    narrow (batch 1) and wide (batch 16: one M tile; batch 64: four) persistent kernels and the
-    per-position launches.  With w_long = 1 a masked token is never drafted, and a row that keeps a
+    narrow (batch 1) and wide (batch 16) persistent kernels and the per-position launches (batch 64, and
+    unprepared heads).  With w_long = 1 a masked token is never drafted, and a row that keeps a
     single finite entry drafts that entry; with w_long = 0 the long term, masks included, is absent
     (the head alone decides).  Statistics against the oracle within the tolerance."""
     p = _problem(name, "stress")
@@ -171,8 +171,9 @@ def test_masked_long_logits(name, w_long, prepared):
 
 
 # ---------------------------------------------------------------------------------------------
-# persistent kernel on small shapes (oracle in seconds): ragged vocabularies, few tiles per CU,
-# both first-row readings, the prior, float32 long logits, batches spanning several 16-slot tiles
+# prepared heads on small shapes (oracle in seconds): ragged vocabularies, few tiles per CU, both
+# first-row readings, the prior, float32 long logits; the persistent kernel up to 16 sequences, launches per
+# position above
 # ---------------------------------------------------------------------------------------------
 SMALL = [
     dict(V=5003, d=96, H=128, r=128, Bk=7, batch=3),
@@ -195,7 +196,7 @@ def test_persistent_small(shape, literal):
 
 EXTREME = [
     dict(V=4099, d=64, H=128, r=128, Bk=64, batch=3),     # the longest block (64 positions)
-    dict(V=1031, d=64, H=128, r=128, Bk=64, batch=64),    # the largest batch with the longest block
+    dict(V=1031, d=64, H=128, r=128, Bk=64, batch=64),    # many sequences with the longest block (launches)
     dict(V=2053, d=64, H=128, r=128, Bk=1, batch=5),      # a single position
 ]
 
@@ -211,9 +212,9 @@ def test_persistent_extreme_block_sizes(shape):
 
 @pytest.mark.parametrize("batch", [65, 256])
 def test_batches_split_into_launches(batch):
-    """Above 64 sequences (up to the ABI's maximum of 256) a prepared head runs consecutive
-    persistent launches of at most 64 sequences on one workspace; the first and last sequence of
-    every launch are compared, greedy and with the prior and the literal first row."""
+    """Above 64 sequences (up to the ABI's maximum of 256) a vocabulary launch of a prepared head has one row of
+    workgroups per 64 sequences; the first and last sequence of each are compared, greedy and with the
+    prior and the literal first row."""
     p = _problem("qwen3-8b-b16", "stress", dtype="bf16", V=2053, d=64, H=128, r=128, Bk=3, batch=batch)
     seqs = sorted({s for b0 in range(0, batch, 64) for s in (b0, min(b0 + 63, batch - 1))})
     tok, st = _draft(p, 0.6, prepared=True, expect_path=1)
@@ -224,10 +225,9 @@ def test_batches_split_into_launches(batch):
 
 @pytest.mark.parametrize("batch", [4, 5, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63])
 def test_batch_sweep_across_m_tiles(batch):
-    """Every batch size on either side of the narrow/wide switch (4 | 5) and of each 16-sequence M
-    tile boundary, where the token merge changes hands (one M tile: every GRU workgroup merges;
-    several: workgroup NG + b merges sequence b), every sequence compared, greedy and with the
-    prior and the literal first row."""
+    """Every batch size on either side of the narrow/wide switch of the persistent kernel (4 | 5), of the
+    switch to launches per position (16 | 17) and of each 16-sequence tile boundary there, every
+    sequence compared, greedy and with the prior and the literal first row."""
     p = _problem("qwen3-8b-b16", "stress", dtype="bf16", V=2053, d=64, H=128, r=128, Bk=3, batch=batch)
     tok, st = _draft(p, 0.6, prepared=True, expect_path=1)
     check_draft(tok, st, p["oracle"], p["long_h"], p["last"], None, 1.0, 0.6, 0.0)
@@ -236,9 +236,9 @@ def test_batch_sweep_across_m_tiles(batch):
 
 
 def test_split_launches_sample_by_sequence_index():
-    """Sampling keys the noise by the sequence's index in the whole call: at batch 80 (launches of
-    64 and 16 sequences) the draws of sequences 63, 64 and 79 are the oracle's for that index, and
-    a sequence drafts the same tokens whether the call is split or not."""
+    """Sampling keys the noise by the sequence's index in the whole call: at batch 80 (two rows of
+    workgroups, of 64 and 16 sequences) the draws of sequences 63, 64 and 79 are the oracle's for that index,
+    and a sequence drafts the same tokens with the prepared head as without."""
     p = _problem("qwen3-8b-b16", "stress", dtype="bf16", V=2053, d=64, H=128, r=128, Bk=4, batch=80)
     head = _head(p, True)
     lt = B.as_tensor(p["long_h"])
@@ -248,7 +248,7 @@ def test_split_launches_sample_by_sequence_index():
     tok, st = tok.cpu().numpy(), st.cpu().numpy()
     check_draft(tok, st, p["oracle"], p["long_h"], p["last"], None, 1.0, 0.6, 0.0,
                 sequences=[0, 63, 64, 79], temperature=1.0, seed=99)
-    # the unsplit per-position launches on the same call draw the same noise
+    # the launches with the unprepared head draw the same noise
     tok2, _ = B.draft_block(p["head"], lt, last, None, 1.0, 0.6, 0.0, temperature=1.0, seed=99)
     torch.cuda.synchronize()
     same = (tok2.cpu().numpy() == tok).all(axis=1)

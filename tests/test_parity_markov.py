@@ -4,8 +4,9 @@ rho_j = E_M[u_j], l_S = W_M rho_j) against the oracle.
 * the hand-worked three-position example (V = 3) with its printed tokens, gaps, scores and
   log-probabilities, and its variants (long logits alone, head alone, literal first row, prior);
 * random Markov heads at the Qwen3 vocabulary, through the per-position launches and the
-  persistent kernel, for narrow (1, 3), wide (16) and multi-tile (37) batches, both first-row
-  readings, the prior and float32 long logits;
+  persistent kernel, for narrow (1, 3), wide (16) and multi-tile batches (17, 24, 32 and 48: the delegated
+  token merge; 37 and 100 of a small vocabulary: launches), both first-row readings, the prior and float32
+  long logits;
 * repeated calls on one workspace are bit-identical.
 """
 import math
@@ -90,7 +91,11 @@ CASES = [
     dict(V=W.QWEN3_VOCAB, r=256, batch=16, Bk=16, seed=72),
     dict(V=5003, r=128, batch=37, Bk=5, seed=73),
     dict(V=7001, r=256, batch=2, Bk=9, seed=74),
-    dict(V=5003, r=128, batch=100, Bk=4, seed=75),        # prepared: launches of 64 and 36 sequences
+    dict(V=5003, r=128, batch=100, Bk=4, seed=75),        # two rows of workgroups, of 64 and 36 sequences
+    dict(V=5003, r=128, batch=17, Bk=5, seed=76),         # prepared: two tiles of the persistent kernel, a ragged one
+    dict(V=W.QWEN3_VOCAB, r=256, batch=24, Bk=5, seed=77),
+    dict(V=5003, r=128, batch=32, Bk=5, seed=78),         # two full tiles
+    dict(V=W.QWEN3_VOCAB, r=256, batch=48, Bk=8, seed=79),   # three
 ]
 
 
@@ -149,8 +154,8 @@ def test_markov_f32_long_logits_and_repeat():
 
 @pytest.mark.parametrize("with_prior", [False, True])
 def test_markov_b64_full_size(with_prior):
-    """The Markov head at the batch-64 serving shape (V = 151,936, r = 256; prepared, four M
-    tiles and the delegated token merge), greedy, with and without the Zipf prior, every sequence."""
+    """The Markov head at the batch-64 serving shape (V = 151,936, r = 256; prepared, launches per
+    position), greedy, with and without the Zipf prior, every sequence."""
     wl = W.WORKLOADS["b64-d5120"]
     em, wm = W.make_markov_head(wl.V, wl.r, "bf16", 92, scale=math.sqrt(3.0 / math.sqrt(wl.r)))
     head = B.LocalHead.markov_from_weights(em, wm).prepare()

@@ -1,7 +1,8 @@
-"""Heads drafted with as they are, at the sizes where the per-position kernels change their ways:
-operand tiles of 16 rows and 16 sequences, chunks of 32 (bf16) or 16 (float32) columns, five hidden units
-per workgroup, the vocabulary slice of a workgroup, the register form (r <= 256) and the LDS form above,
-one, two, four and more tiles of sequences, and the single-workgroup form of small heads.  Tokens and
+"""Heads drafted with by launches per position (as they are, and prepared ones of many sequences), at the sizes
+where the per-position kernels change their ways: operand tiles of 16 rows and 16 sequences, chunks of 32 (bf16) or
+16 (float32) columns, five hidden units per workgroup or one per wave, the vocabulary slice of a workgroup, the
+register form (r <= 256) and the LDS form above, one, two, four and more tiles of sequences, and the
+single-workgroup form of small heads on either side of its rule.  Tokens and
 statistics against the oracle, and statistics within 2e-4 absolute: the logits here stay below about 100,
 float32 products and sums keep about 1e-6 relative."""
 import math
