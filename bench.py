@@ -98,6 +98,14 @@ def measured_traffic(workload):
                             if "dram_read_bytes_per_launch" in rec else {})
 
 
+def route_of(path, ws, torch):
+    """The route the calls on workspace `ws` took (at least one before): the persistent kernel advances the call
+    epoch in its first word."""
+    if path != 1:
+        return "per-position launches"
+    return "persistent" if int(ws[:4].view(torch.int32).item()) > 0 else "prepared, per-position launches"
+
+
 def pct(xs, q):
     import numpy as np
     return float(np.percentile(np.asarray(xs, dtype=np.float64), q))
@@ -302,8 +310,7 @@ def time_workload(B, W, wl, dev, torch, n=100):
     alg, _ = algorithmic_bytes(wl, 2 if wl.dtype == "bf16" else 4)
     comp = compulsory_bytes(wl, 2 if wl.dtype == "bf16" else 4)
     return {"batch": wl.batch, "B": wl.B, "V": V, "d": d, "H": H, "r": r, "dtype": wl.dtype,
-            "path": ("persistent" if wl.batch <= 16 else "prepared, per-position launches") if path == 1
-                    else "per-position launches", "us_per_block": dist(us),
+            "path": route_of(path, ws, torch), "us_per_block": dist(us),
             "tokens_per_s": round(wl.batch * wl.B / (med * 1e-6), 1), "us_per_position": round(med / wl.B, 2),
             "algorithmic_bytes_per_block": alg, "roofline_frac": round(alg / (med * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
             "compulsory_frac": round(comp / (med * 1e-6) / 1e9 / HBM_PEAK_GBS, 4),
@@ -363,7 +370,6 @@ def main():
     torch.cuda.synchronize()
     L = B.as_tensor(long_h, dev)
     path = head.path(wl.batch, wl.B, L.dtype, False)
-    log(f"draft path: {('persistent' if wl.batch <= 16 else 'prepared, per-position launches') if path == 1 else 'per-position launches'}")
     last_t = torch.from_numpy(last).to(dev)
     tok = torch.empty((wl.batch, wl.B), dtype=torch.int32, device=dev)
     st = torch.empty((wl.batch, wl.B, 6), dtype=torch.float32, device=dev)
@@ -421,7 +427,8 @@ def main():
     ms_step = e0.elapsed_time(e1) / args.steps
     tokens_per_s = wl.batch * wl.B / (ms_step * 1e-3)
     assert B.workspace_error(ws) == 0, "persistent kernel reported an error"
-    log(f"step {ms_step * 1e3:.1f} us ({wall:.2f} s wall) -> {tokens_per_s:.0f} drafted tokens/s")
+    route = route_of(path, ws, torch)
+    log(f"step {ms_step * 1e3:.1f} us ({wall:.2f} s wall, {route}) -> {tokens_per_s:.0f} drafted tokens/s")
 
     # ---- the dominant kernel: per-call distributions, warm and cold -------------------------------
     warm = per_call_us(draft, args.calls, torch)
@@ -434,11 +441,11 @@ def main():
     comp = compulsory_bytes(wl)
     flops = method_flops(wl)
     achieved = alg_block / (blk_us * 1e-6) / 1e9
-    traffic = measured_traffic(wl.name) if path == 1 else None
+    traffic = measured_traffic(wl.name) if route == "persistent" else None
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic["traffic_bytes_per_launch"] if traffic else None,
-                "kernel": "k_draft_persistent (one launch per block)" if path == 1 and wl.batch <= 16 else
+                "kernel": "k_draft_persistent (one launch per block)" if route == "persistent" else
                           "dls_draft_block (all launches of one block)",
                 "us_per_launch": round(blk_us, 2),
                 "algorithmic_bytes_per_launch": alg_block,
@@ -464,20 +471,20 @@ def main():
 
     extras = {}
     if not args.no_extras:
-        # the other launch mode (cooperative vs ordinary dispatch)
-        if not args.no_cooperative_comparison:
+        # the other launch mode of the persistent kernel (cooperative vs ordinary dispatch)
+        if not args.no_cooperative_comparison and route == "persistent":
             for _ in range(3):
                 draft(exclusive=not EXC)
             other = per_call_us(lambda i: draft(exclusive=not EXC), 30, torch)
             extras["draft_block_" + ("cooperative" if EXC else "ordinary") + "_launch_us"] = dist(other)
             log(f"draft block with {'a cooperative' if EXC else 'an ordinary'} launch: {pct(other, 50):.1f} us")
-        # the same block without row statistics (Algorithm 1 needs only the tokens): the kernel
-        # then skips the statistics reduction and publish of every M tile
+        # the same block without row statistics (Algorithm 1 needs only the tokens): the kernels
+        # then skip the log-sum-exps
         tonly = per_call_us(lambda i: B.draft_block(head, L, last_t, None, 1.0, args.alpha, 0.0, out=(tok, None),
                                                     workspace=ws, exclusive_device=EXC), 30, torch)
         extras["draft_block_tokens_only_us"] = dist(tonly)
         log(f"draft block without row statistics: {pct(tonly, 50):.1f} us")
-        # the same block through the per-position launches (no prepared head)
+        # the same block with the head as it is
         base_head = B.LocalHead(head.emb, head.w_ih, head.w_hh, head.w_rank, head.w_vocab)
         ws2 = B.draft_workspace(base_head, wl.batch, wl.B, dev)
         pp = per_call_us(lambda i: B.draft_block(base_head, L, last_t, None, 1.0, args.alpha, 0.0, out=(tok, st),
@@ -641,7 +648,8 @@ def main():
         "config": {"workload": wl.name, "batch": wl.batch, "B": wl.B, "V": wl.V, "d": wl.d, "H": wl.H,
                    "r": wl.r, "weights": f"bf16 ({args.init} init)", "alpha": args.alpha, "beta": 0.0,
                    "step": "draft_block + accept_len",
-                   "launch": "ordinary dispatch (DLS_EXCLUSIVE_DEVICE)" if EXC else "cooperative"},
+                   "launch": route if route != "persistent" else
+                             "ordinary dispatch (DLS_EXCLUSIVE_DEVICE)" if EXC else "cooperative"},
         "roofline": roofline,
         "measured_peaks": peaks,
         "cpu_baseline": cpu,
