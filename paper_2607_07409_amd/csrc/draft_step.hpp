@@ -508,13 +508,14 @@ __global__ __launch_bounds__(kRT) void k_gates_rows(GatesArgs<WT> a) {
     if (p + 64 * kU < np) load_w(a.w_ih, d, np, p + 64 * kU);
 #pragma unroll
     for (int u = 0; u < kU; ++u) {
-      const bool ok = p + u * 64 + lane < np;
+      if (p + u * 64 + lane < np) {   // not the clamped pieces: a zero would not take an infinite weight out
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        float xv[N];
-        Chunk<WT>::widen(sel4(ok, x[b][u]), xv);
+        for (int b = 0; b < NB; ++b) {
+          float xv[N];
+          Chunk<WT>::widen(x[b][u], xv);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) fma_row(acc[q][b], c[q][u], xv);
+          for (int q = 0; q < 3; ++q) fma_row(acc[q][b], c[q][u], xv);
+        }
       }
     }
   }

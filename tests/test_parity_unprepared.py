@@ -173,6 +173,21 @@ def test_log_sum_exp_precision(prepared, batch):
     assert err.mean() < 3e-7
 
 
+@pytest.mark.parametrize("batch,dt", [(1, "bf16"), (2, "f32"), (4, "bf16")])
+def test_infinite_gate_weight(batch, dt):
+    """An infinite weight in the last column closes or opens its gate; nothing past the ragged end of a row may meet it."""
+    wl = W.WORKLOADS["qwen3-8b-b16"].with_(V=5003, d=72, H=72, r=64, B=3, batch=batch, dtype=dt, seed=9)
+    hw = W.make_head(wl, "stress")
+    bits, inf = (hw.w_ih.bits, 0x7F80) if dt == "bf16" else (hw.w_ih, np.inf)
+    bits[72 + 5, -1] = inf
+    head, oracle = B.LocalHead.from_weights(hw), O.RnnHead.from_weights(hw)
+    long_h, last = W.make_long_logits(wl), W.make_last_token(wl)
+    tok, st = B.draft_block(head, B.as_tensor(long_h), torch.from_numpy(np.asarray(last, np.int32)).cuda(), None, 1.0, 0.5, 0.0)
+    with np.errstate(over="ignore"):
+        rep = check_draft(tok.cpu().numpy(), st.cpu().numpy(), oracle, long_h, last, None, 1.0, 0.5, 0.0)
+    assert all(np.isfinite(e) and e < 2e-4 for e in rep["errs"].values()), rep["errs"]
+
+
 @pytest.mark.parametrize("prepared,batch,T", [(False, 3, 0.7), (True, 20, 0.0), (True, 40, 0.7), (False, 20, 0.0)])
 def test_no_long_term(prepared, batch, T):
     """w_long = 0 with masked long logits: the long term is absent, masks included, and the head and the prior
